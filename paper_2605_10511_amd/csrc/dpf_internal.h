@@ -249,9 +249,12 @@ struct HashBuildArgs {
     int32_t pad2;
 };
 
-// Launchers (kernels.hip).  Each returns the hipError_t of the launch.
-// waves: 4, 8 or 16 waves per workgroup.
+// Launchers.  Each returns the hipError_t of the launch.
+// waves: 4, 8 or 16 waves per workgroup.  launch_fused picks the instantiation
+// for the batch's string atoms (str_stage), each in a source file of its own.
 hipError_t launch_fused(const BatchArgs& a, int waves, int grid, size_t lds_bytes, hipStream_t s);
+hipError_t launch_fused_str(const BatchArgs& a, int waves, int grid, size_t lds_bytes, hipStream_t s);
+hipError_t launch_fused_fsst(const BatchArgs& a, int waves, int grid, size_t lds_bytes, hipStream_t s);
 // Per-wave LDS the fused kernel needs (survivor queue, string row offsets).
 size_t fused_wave_area_bytes(bool str, bool pend);
 hipError_t launch_hash_count(const HashBuildArgs* d_args, int grid, hipStream_t s);
