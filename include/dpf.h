@@ -319,9 +319,8 @@ typedef struct {
  * up to 2^22 slots; above that it is an open-addressing hash table in
  * device memory whose slot count is a power of two at least twice
  * min(range, table rows), at most 2^22 slots, as the direct table (else
- * DPF_ERR_UNSUPPORTED, as for a range above 2^62): the workgroup that
- * finishes last scans the table to emit the records.  Executing the plan then allocates nothing and
- * can be captured in a HIP graph.  The device
+ * DPF_ERR_UNSUPPORTED, as for a range above 2^62).  Executing the plan then
+ * allocates nothing and can be captured in a HIP graph.  The device
  * copy of the plan (its descriptor, the surviving-block list and the zeroed
  * workspace) is enqueued on the context's own upload stream from pinned
  * staging, and the call returns without waiting for it: every execution
@@ -369,7 +368,8 @@ typedef struct {
 
 /* Enqueues n >= 1 plans on stream.  FUSED runs them all in ONE launch of the
  * persistent kernel, which claims (plan, row range) work items from a device
- * queue; FRAGMENTED runs each plan as a sequence of separate kernels with
+ * queue (a plan whose group table is hashed or exceeds 8,192 accumulators
+ * has its records written by a second, small launch); FRAGMENTED runs each plan as a sequence of separate kernels with
  * materialised intermediates (it allocates on first use and is not meant for
  * graph capture).  FUSED with n <= 64 allocates no device memory and is
  * graph-capturable.  Outside stream capture the call records a completion

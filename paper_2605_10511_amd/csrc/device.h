@@ -1127,43 +1127,32 @@ __device__ __forceinline__ unsigned long long ld_acq(const unsigned long long* p
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Write a plan's non-empty groups as records [group, acc...] into its pinned
-// host buffer (paper Section 3.1: the aggregate is converted into a record
-// format and returned to the host), then clear the device table T (and a
-// hash table's keys) and the status word for the next execution.  Run by
-// one workgroup after every other one has finished.
-__device__ void emit_records(CQ& Q, int32_t* ctrl, unsigned long long* T, uint32_t* status) {
-    const int nacc = Q.nacc;
-    const int64_t G = Q.ngroups;
-    unsigned long long* K = Q.agg_hash ? T + G * nacc : nullptr;
-    if (threadIdx.x == 0) ctrl[2] = 0;
-    __syncthreads();
-    for (int64_t g = threadIdx.x; g < G; g += blockDim.x) {
-        unsigned long long key = 0;
-        if (K) {
-            key = ld_acq(&K[g]);
-            if (key == 0) continue;
-            K[g] = 0;
-        }
-        unsigned long long cnt = ld_acq(&T[g * nacc]);
-        if (cnt == 0) continue;
-        int pos = atomicAdd(&ctrl[2], 1);
-        int64_t* rec = Q.host_out + 2 + (int64_t)pos * (1 + nacc);
-        rec[0] = K ? (int64_t)(key - 1ull) : g;
-        rec[1] = (int64_t)cnt;
-        T[g * nacc] = 0;
-        for (int a = 1; a < nacc; ++a) {
-            rec[1 + a] = (int64_t)ld_acq(&T[g * nacc + a]);
-            T[g * nacc + a] = 0;
-        }
+// Copy a small direct group table T to the plan's pinned host buffer (paper
+// Section 3.1: the aggregate is returned to the host) and clear it and the
+// status word for the next execution.  The table goes out whole, empty
+// groups included: the host drops those.  A compaction would put a count, a
+// position and then one load after the other in series for each group, about
+// 1 us each; here all loads of up to four entries a thread wait once.  Run
+// by nthreads threads (tid among them) after every workgroup has finished.
+__device__ void emit_table(CQ& Q, unsigned long long* T, uint32_t* status, int tid, int nthreads) {
+    const int n = (int)Q.ngroups * Q.nacc;  // at most kEmitEntries
+    int64_t* out = Q.host_out + 2;
+    for (int e0 = tid; e0 < n; e0 += 4 * nthreads) {
+        unsigned long long v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = e0 + k * nthreads < n ? ld_acq(&T[e0 + k * nthreads]) : 0ull;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (e0 + k * nthreads < n) {
+                out[e0 + k * nthreads] = (int64_t)v[k];
+                T[e0 + k * nthreads] = 0;
+            }
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t st = __hip_atomic_exchange(status, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) {
+        const uint32_t st = __hip_atomic_exchange(status, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         Q.host_out[0] = (int64_t)st;
-        Q.host_out[1] = (int64_t)ctrl[2];
+        Q.host_out[1] = 1;  // the table is present
     }
-    __syncthreads();
 }
 }  // namespace
 }  // namespace dpf

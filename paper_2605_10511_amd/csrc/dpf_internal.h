@@ -25,7 +25,12 @@ constexpr int kMaxBatch = 64;     // plans per fused launch
 constexpr int kMaxHashCols = 8;   // dimension columns per hash build
 constexpr int kMaxHashPreds = 8;  // dimension predicates per hash build
 constexpr int64_t kMaxGroups = int64_t(1) << 22;  // direct-indexed group table limit
-constexpr int64_t kMaxHashSlots = int64_t(1) << 22;  // hash group table limit (slots; one workgroup emits it)
+constexpr int64_t kMaxHashSlots = int64_t(1) << 22;  // hash group table limit (slots)
+// A direct group table of at most this many entries (groups x accumulators)
+// is copied to the host whole by the fused kernel's last workgroup; a larger
+// or hashed one is compacted by emit_kernel, a second launch (about 5 us,
+// the time that workgroup takes to copy this many entries).
+constexpr int64_t kEmitEntries = 8192;
 constexpr int64_t kMaxGroupDomain = int64_t(1) << 62;  // group index + 1 fits int64
 constexpr int32_t kEmptyKey = INT32_MIN;
 constexpr int kXcds = 8;             // XCDs per device; workgroup i is dispatched to XCD i % 8
@@ -171,7 +176,7 @@ struct DevQuery {
     int32_t lds_shared;  // LDS bytes of this plan's shared area (hashes + table)
     int32_t has_str;
     int32_t agg_hash;
-    int32_t agg_pad;
+    int32_t emit_copy;   // the last workgroup copies the whole table to the host (kEmitEntries)
     // The string atom on an FSST column (index into preds, -1: none): its
     // byte automaton (fs_states rows of 256 next states, device memory) and
     // the byte offset of its code table ((2 fs_states + 1) rows of 256) in
@@ -181,8 +186,10 @@ struct DevQuery {
     int32_t fs_states;
     int32_t fs_pad;
     const uint8_t* fs_dfa;
-    uint32_t* status;    // device status bits (ST_*)
-    int64_t* host_out;   // device address of the pinned output: [status, nrec, records...]
+    uint32_t* status;    // device: status bits (ST_*), emit_kernel's record and workgroup counts
+    // Device address of the pinned output: [status, 1, group table] (emit_copy),
+    // else [status, records, groups[ngroups], accumulator 0[ngroups], ...].
+    int64_t* host_out;
     // Chunk pruning: null, or the ascending indices of the blocks of
     // prune_mb mini blocks that the zone maps do not exclude; the fused
     // kernel's work items then cover those blocks only.
@@ -259,6 +266,9 @@ hipError_t launch_fused_fsst(const BatchArgs& a, int waves, int grid, size_t lds
 size_t fused_wave_area_bytes(bool str, bool pend);
 hipError_t launch_hash_count(const HashBuildArgs* d_args, int grid, hipStream_t s);
 hipError_t launch_hash_insert(const HashBuildArgs* d_args, int grid, hipStream_t s);
+// Emits and clears a group table that the fused kernel does not copy itself
+// (emit_copy 0).  status: the plan's status words.
+hipError_t launch_emit(const DevQuery* d_q, const DevQuery& h_q, int64_t* agg, uint32_t* status, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 // Bandwidth probe: grid x 256 lanes read bytes (a multiple of 16) at p.
 hipError_t launch_stream_read(const void* p, uint64_t bytes, uint32_t key, uint32_t* sink, int grid,

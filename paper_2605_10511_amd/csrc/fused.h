@@ -7,7 +7,7 @@
 // against the dimension hash tables (LDS copies for small ones) and
 // aggregated into a per-workgroup LDS table.  The last workgroup to finish
 // writes the records to the host buffer -- nothing is materialised in
-// between.
+// between (group tables above kEmitEntries entries go out through emit_kernel).
 #pragma once
 #include "device.h"
 
@@ -538,8 +538,16 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(kStr
     __syncthreads();
     if (!ctrl[1]) return;
     __threadfence();
-    for (int qi = 0; qi < a.nq; ++qi)
-        emit_records(*ro(a.q[qi]), ctrl, reinterpret_cast<unsigned long long*>(a.agg[qi]), a.status[qi]);
+    // One wave a plan where the batch has more plans than the workgroup waves
+    // (each plan's copy is mostly one wait for memory), else all threads on
+    // each plan in turn.  Larger tables are left to emit_kernel.
+    const bool by_wave = a.nq >= nw;
+    for (int qi = by_wave ? wave : 0; qi < a.nq; qi += by_wave ? nw : 1) {
+        CQ& Q = *ro(a.q[qi]);
+        if (!Q.emit_copy) continue;
+        emit_table(Q, reinterpret_cast<unsigned long long*>(a.agg[qi]), a.status[qi],
+                   by_wave ? lane : (int)threadIdx.x, by_wave ? kWave : (int)blockDim.x);
+    }
     if (threadIdx.x < 2 * kXcds + 1)  // every other workgroup has left: reset for the next launch
         __hip_atomic_store(ctr(a, threadIdx.x), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __threadfence_system();

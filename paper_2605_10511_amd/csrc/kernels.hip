@@ -2,6 +2,7 @@
 // than the fused one (fused.h).
 //
 //  * hash_count / hash_insert: the build side (Section 3.1, Kernel #1).
+//  * emit_kernel: the records of a large group table to the host.
 //  * frag_*: the plan as separate kernels with materialised intermediates
 //    (Section 5.1, the multi-kernel baseline).
 #include "device.h"
@@ -157,6 +158,81 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const uint4* __restric
         acc ^= x.x ^ x.y ^ x.z ^ x.w;
     }
     if (acc == key) sink[0] = acc;
+}
+
+// Writes the non-empty groups of a large or hashed group table to the plan's
+// pinned host buffer and clears them and the status words for the next
+// execution.  Bound by the scan of the slots (32 MB for 2^22 hash slots) and
+// the records' way over the host link, so the slots are cut into slabs of
+// kEmitSlab over many workgroups; one workgroup alone took 21 ms for 2^22
+// slots.  Each workgroup reserves a slab's output with one atomic.  The
+// buffer is one array per record field (the group, then each accumulator):
+// a wave's stores are then contiguous runs of 8 bytes a lane, where whole
+// records would cross the link as scattered 8-byte writes.  The host orders
+// the groups.  status: [bits, records so far, finished workgroups].
+constexpr int kEmitBlock = 1024, kEmitSlots = 8, kEmitSlab = kEmitBlock * kEmitSlots;
+
+__global__ __launch_bounds__(kEmitBlock) void emit_kernel(const DevQuery* __restrict__ q, unsigned long long* T,
+                                                          uint32_t* status) {
+    __shared__ uint32_t wcnt[kEmitBlock / kWave];
+    __shared__ uint32_t base_s;
+    CQ& Q = *ro(q);
+    const int nacc = Q.nacc;
+    const int64_t G = Q.ngroups;
+    unsigned long long* const K = Q.agg_hash ? T + G * nacc : nullptr;
+    int64_t* const out = Q.host_out + 2;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    for (int64_t s0 = (int64_t)blockIdx.x * kEmitSlab; s0 < G; s0 += (int64_t)gridDim.x * kEmitSlab) {
+        unsigned long long key[kEmitSlots], cnt[kEmitSlots];
+#pragma unroll
+        for (int k = 0; k < kEmitSlots; ++k) {
+            const int64_t g = s0 + k * kEmitBlock + threadIdx.x;
+            key[k] = g < G ? (K ? K[g] : (unsigned long long)g + 1ull) : 0ull;
+        }
+        uint32_t mine = 0;
+#pragma unroll
+        for (int k = 0; k < kEmitSlots; ++k) {
+            const int64_t g = s0 + k * kEmitBlock + threadIdx.x;
+            cnt[k] = key[k] ? T[g * nacc] : 0ull;
+            if (K && key[k]) K[g] = 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kEmitSlots; ++k) mine += (uint32_t)__popcll(__ballot(cnt[k] != 0));  // the wave's
+        if (lane == 0) wcnt[wave] = mine;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t t = 0;
+            for (int w = 0; w < kEmitBlock / kWave; ++w) { const uint32_t x = wcnt[w]; wcnt[w] = t; t += x; }
+            base_s = t ? atomicAdd(&status[1], t) : 0u;
+        }
+        __syncthreads();
+        uint32_t o = base_s + wcnt[wave];
+#pragma unroll
+        for (int k = 0; k < kEmitSlots; ++k) {
+            const uint64_t b = __ballot(cnt[k] != 0);
+            if (cnt[k]) {
+                const int64_t g = s0 + k * kEmitBlock + threadIdx.x;
+                const int64_t pos = o + bits_below(b);
+                out[pos] = (int64_t)(key[k] - 1ull);
+                out[G + pos] = (int64_t)cnt[k];
+                T[g * nacc] = 0;
+                for (int a = 1; a < nacc; ++a) {
+                    out[(1 + a) * G + pos] = (int64_t)T[g * nacc + a];
+                    T[g * nacc + a] = 0;
+                }
+            }
+            o += (uint32_t)__popcll(b);
+        }
+        __syncthreads();  // wcnt and base_s are rewritten by the next slab
+    }
+    // Thread 0 has the values its reservations returned, so they precede its
+    // count here: the last one reads the total.
+    if (threadIdx.x == 0 && atomicAdd(&status[2], 1u) == gridDim.x - 1u) {
+        Q.host_out[1] = (int64_t)atomicExch(&status[1], 0u);
+        Q.host_out[0] = (int64_t)atomicExch(&status[0], 0u);
+        atomicExch(&status[2], 0u);
+        __threadfence_system();
+    }
 }
 
 template <typename T>
@@ -655,10 +731,8 @@ __global__ __launch_bounds__(kBlock) void frag_aggregate(const DevQuery* __restr
 }
 
 __global__ __launch_bounds__(kBlock) void frag_emit(const DevQuery* __restrict__ q) {
-    __shared__ int32_t ctrl[4];
     CQ& Q = *ro(q);
-    __threadfence();
-    emit_records(Q, ctrl, reinterpret_cast<unsigned long long*>(Q.agg), Q.status);
+    emit_table(Q, reinterpret_cast<unsigned long long*>(Q.agg), Q.status, threadIdx.x, blockDim.x);
     __threadfence_system();
 }
 
@@ -681,6 +755,13 @@ hipError_t launch_stream_read(const void* p, uint64_t bytes, uint32_t key, uint3
                               hipStream_t s) {
     hipLaunchKernelGGL(stream_read_kernel, dim3(grid), dim3(256), 0, s, reinterpret_cast<const uint4*>(p),
                        (uint64_t)(bytes / 16), key, sink);
+    return hipGetLastError();
+}
+
+hipError_t launch_emit(const DevQuery* d_q, const DevQuery& h_q, int64_t* agg, uint32_t* status, hipStream_t s) {
+    const int64_t slabs = (h_q.ngroups + kEmitSlab - 1) / kEmitSlab;
+    hipLaunchKernelGGL(emit_kernel, dim3((int)(slabs < 1024 ? slabs : 1024)), dim3(kEmitBlock), 0, s, d_q,
+                       reinterpret_cast<unsigned long long*>(agg), status);
     return hipGetLastError();
 }
 
@@ -765,8 +846,13 @@ int run_fragmented(const DevQuery* d_q, const DevQuery& Q, const FragBuffers& fb
     hipLaunchKernelGGL(frag_aggregate, dim3(grid), dim3(kBlock), 0, s, d_q, fb.rows[src], &fb.counts[Q.nprobes],
                        fb, src);
     if (!chk()) return -1;
-    hipLaunchKernelGGL(frag_emit, dim3(1), dim3(kBlock), 0, s, d_q);
-    if (!chk()) return -1;
+    if (Q.emit_copy) {
+        hipLaunchKernelGGL(frag_emit, dim3(1), dim3(kBlock), 0, s, d_q);
+        if (!chk()) return -1;
+    } else {
+        if (launch_emit(d_q, Q, Q.agg, Q.status, s) != hipSuccess) return -1;
+        ++launches;
+    }
     return launches;
 }
 
