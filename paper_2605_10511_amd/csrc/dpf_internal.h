@@ -243,7 +243,10 @@ struct HashBuildArgs {
     unsigned long long* count;  // qualifying rows
     long long* mm;              // [0..1] key min/max, [2..5] payload min/max
     uint32_t* status;
-    // insert pass
+};
+
+// The table that the insert pass fills.
+struct HashTableArgs {
     int32_t* keys;
     void* pay[2];
     int32_t pay64[2];
@@ -253,7 +256,6 @@ struct HashBuildArgs {
     int64_t bmin;
     uint32_t* filt;     // bit filter (nullptr: none)
     int32_t flog2;
-    int32_t pad2;
 };
 
 // Launchers.  Each returns the hipError_t of the launch.
@@ -265,7 +267,9 @@ hipError_t launch_fused_fsst(const BatchArgs& a, int waves, int grid, size_t lds
 // Per-wave LDS the fused kernel needs (survivor queue, string row offsets).
 size_t fused_wave_area_bytes(bool str, bool pend);
 hipError_t launch_hash_count(const HashBuildArgs* d_args, int grid, hipStream_t s);
-hipError_t launch_hash_insert(const HashBuildArgs* d_args, int grid, hipStream_t s);
+hipError_t launch_hash_insert(const HashBuildArgs* d_args, const HashTableArgs& t, int grid, hipStream_t s);
+// p[0 .. nkeys) = kEmptyKey, p[zero_from .. nwords) = 0.
+hipError_t launch_hash_clear(int32_t* p, int64_t nkeys, int64_t zero_from, int64_t nwords, hipStream_t s);
 // Emits and clears a group table that the fused kernel does not copy itself
 // (emit_copy 0).  status: the plan's status words.
 hipError_t launch_emit(const DevQuery* d_q, const DevQuery& h_q, int64_t* agg, uint32_t* status, hipStream_t s);

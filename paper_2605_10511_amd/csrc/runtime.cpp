@@ -758,35 +758,45 @@ extern "C" dpf_status dpf_hash_build(dpf_ctx ctx, const dpf_hash_desc* desc, dpf
     A.nrows = nrows;
     A.nmb = (int32_t)desc->cols[0]->host.nmb;
 
-    // scratch: [args][count u64][mm 6 x i64][status]
+    // scratch: [args][count u64][mm 6 x i64][status], copied in one piece from
+    // a pinned block, which also takes the results back
     const size_t args_off = 0, cnt_off = align_up(sizeof(HashBuildArgs), 256), mm_off = cnt_off + 64,
                  st_off = mm_off + 64, scratch_bytes = st_off + 64;
+    struct Guard {
+        dpf_ctx c; void* p; int kind;
+        ~Guard() { c->free_mem(p, kind); }
+    };
     uint8_t* scratch = (uint8_t*)ctx->alloc_mem(scratch_bytes, DPF_MEM_HBM);
     if (!scratch) return fail(DPF_ERR_OOM, "hash scratch");
-    struct Guard {
-        dpf_ctx c; void* p;
-        ~Guard() { c->free_mem(p, DPF_MEM_HBM); }
-    } guard{ctx, scratch};
+    Guard guard{ctx, scratch, DPF_MEM_HBM};
+    uint8_t* stage = (uint8_t*)ctx->alloc_mem(scratch_bytes, DPF_MEM_HOST_MAPPED);
+    if (!stage) return fail(DPF_ERR_OOM, "hash staging");
+    Guard stage_guard{ctx, stage, DPF_MEM_HOST_MAPPED};
     A.count = (unsigned long long*)(scratch + cnt_off);
     A.mm = (long long*)(scratch + mm_off);
     A.status = (uint32_t*)(scratch + st_off);
-    long long mm_init[6] = {INT64_MAX, INT64_MIN, INT64_MAX, INT64_MIN, INT64_MAX, INT64_MIN};
-    uint8_t init[192] = {};
-    std::memcpy(init + 64, mm_init, sizeof mm_init);
-    HIP_TRY(hipMemcpyAsync(scratch + cnt_off, init, 192, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(scratch + args_off, &A, sizeof A, hipMemcpyHostToDevice, s));
+    const long long mm_init[6] = {INT64_MAX, INT64_MIN, INT64_MAX, INT64_MIN, INT64_MAX, INT64_MIN};
+    std::memset(stage, 0, scratch_bytes);
+    std::memcpy(stage + args_off, &A, sizeof A);
+    std::memcpy(stage + mm_off, mm_init, sizeof mm_init);
+    // (a failed call leaves the stream drained: the blocks go back to the pool)
+    auto drained = [&](hipError_t e, const char* what) {
+        (void)hipStreamSynchronize(s);
+        return hip_fail(e, what);
+    };
     const int grid = std::max(1, std::min<int>((int)((A.nmb + 3) / 4), ctx->ncu * 8));
-    HIP_TRY(launch_hash_count((const HashBuildArgs*)(scratch + args_off), grid, s));
+    hipError_t e = hipMemcpyAsync(scratch, stage, scratch_bytes, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = launch_hash_count((const HashBuildArgs*)(scratch + args_off), grid, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(stage + cnt_off, scratch + cnt_off, 192, hipMemcpyDeviceToHost, s);
+    if (e != hipSuccess) return drained(e, "hash count");
     ctx->launches++;
-    uint8_t back[192];
-    HIP_TRY(hipMemcpyAsync(back, scratch + cnt_off, 192, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     uint64_t count;
     long long mm[6];
     uint32_t status;
-    std::memcpy(&count, back, 8);
-    std::memcpy(mm, back + 64, sizeof mm);
-    std::memcpy(&status, back + 128, 4);
+    std::memcpy(&count, stage + cnt_off, 8);
+    std::memcpy(mm, stage + mm_off, sizeof mm);
+    std::memcpy(&status, stage + st_off, 4);
     if (status & ST_CORRUPT) return fail(DPF_ERR_CORRUPT, "corrupt dimension column");
 
     int log2cap = 4;
@@ -831,33 +841,33 @@ extern "C" dpf_status dpf_hash_build(dpf_ctx ctx, const dpf_hash_desc* desc, dpf
         delete h;
         return fail(st, m);
     };
-    A.keys = (int32_t*)h->mem;
+    HashTableArgs T{};
+    T.keys = (int32_t*)h->mem;
     for (int j = 0; j < A.npay; ++j) {
-        A.pay[j] = (uint8_t*)h->mem + pay_off[j];
-        A.pay64[j] = pay64[j];
+        T.pay[j] = (uint8_t*)h->mem + pay_off[j];
+        T.pay64[j] = pay64[j];
     }
-    A.cap_mask = (uint32_t)(cap - 1);
-    A.log2cap = log2cap;
-    A.bits = use_bits ? (uint32_t*)((uint8_t*)h->mem + bits_off) : nullptr;
-    A.bmin = use_bits ? mm[0] : 0;
-    hipError_t e = launch_fill_i32((int32_t*)h->mem, kEmptyKey, (int64_t)cap, s);
-    if (e == hipSuccess && use_bits) e = launch_fill_i32((int32_t*)A.bits, 0, (int64_t)bits_words, s);
-    A.filt = flog2 ? (uint32_t*)((uint8_t*)h->mem + filt_off) : nullptr;
-    A.flog2 = flog2;
-    if (e == hipSuccess && flog2) e = launch_fill_i32((int32_t*)A.filt, 0, (int64_t)filt_words, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(scratch + args_off, &A, sizeof A, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = launch_hash_insert((const HashBuildArgs*)(scratch + args_off), grid, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&status, A.status, 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    T.cap_mask = (uint32_t)(cap - 1);
+    T.log2cap = log2cap;
+    T.bits = use_bits ? (uint32_t*)((uint8_t*)h->mem + bits_off) : nullptr;
+    T.bmin = use_bits ? mm[0] : 0;
+    T.filt = flog2 ? (uint32_t*)((uint8_t*)h->mem + filt_off) : nullptr;
+    T.flog2 = flog2;
+    e = launch_hash_clear((int32_t*)h->mem, (int64_t)cap, (int64_t)(bytes / 4), (int64_t)(alloc_bytes / 4), s);
+    if (e == hipSuccess) e = launch_hash_insert((const HashBuildArgs*)(scratch + args_off), T, grid, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(stage + st_off, A.status, 4, hipMemcpyDeviceToHost, s);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
     ctx->launches += 2;
     if (e != hipSuccess) return bail(DPF_ERR_HIP, std::string("hash insert: ") + hipGetErrorString(e));
+    std::memcpy(&status, stage + st_off, 4);
     if (status & ST_DUPLICATE) return bail(DPF_ERR_DUPLICATE_KEY, "duplicate key among qualifying rows");
     if (status & ST_UNSUPPORTED) return bail(DPF_ERR_UNSUPPORTED, "hash keys must fit int32 and differ from INT32_MIN");
     if (status & (ST_CORRUPT | ST_CAPACITY)) return bail(DPF_ERR_CORRUPT, "hash insert failed");
 
     DevHash& d = h->dev;
     d.keys = (const int32_t*)h->mem;
-    for (int j = 0; j < 2; ++j) d.pay[j] = j < A.npay ? A.pay[j] : nullptr;
+    for (int j = 0; j < 2; ++j) d.pay[j] = j < A.npay ? T.pay[j] : nullptr;
     d.cap_mask = (uint32_t)(cap - 1);
     d.log2cap = log2cap;
     d.npay = A.npay;
@@ -865,10 +875,10 @@ extern "C" dpf_status dpf_hash_build(dpf_ctx ctx, const dpf_hash_desc* desc, dpf
     d.pay64[1] = pay64[1];
     d.lds_off = -1;
     d.bytes = (uint32_t)bytes;
-    d.bits = A.bits;
-    d.bmin = A.bmin;
+    d.bits = T.bits;
+    d.bmin = T.bmin;
     d.bspan = use_bits ? kspan : 0;
-    d.filt = A.filt;
+    d.filt = T.filt;
     d.flog2 = flog2;
     d.filt_lds_off = -1;
     d.bits_lds_off = -1;
