@@ -41,7 +41,8 @@ def log(*a):
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2605_10511_amd", "csrc", f) for f in
-                  ("kernels.hip", "device.h", "fused.h", "fused_int.hip", "fused_str.hip", "fused_fsst.hip", "dpf_internal.h")]
+                  ("kernels.hip", "device.h", "fused.h", "fused_lean.hip", "fused_int.hip", "fused_str.hip",
+                   "fused_fsst.hip", "dpf_internal.h")]
 
 
 def kernel_source_sha256() -> str:

@@ -368,10 +368,11 @@ typedef struct {
 
 /* Enqueues n >= 1 plans on stream.  FUSED runs them all in ONE launch of the
  * persistent kernel, which claims (plan, row range) work items from a device
- * queue (a plan whose group table is hashed or exceeds 8,192 accumulators
- * has its records written by a second, small launch); FRAGMENTED runs each plan as a sequence of separate kernels with
- * materialised intermediates (it allocates on first use and is not meant for
- * graph capture).  FUSED with n <= 64 allocates no device memory and is
+ * queue (two launches where some plans have probes or string atoms and the
+ * others scan 2M rows or more; a plan whose group table is hashed or exceeds
+ * 8,192 accumulators has its records written by a small launch more);
+ * FRAGMENTED runs each plan as a sequence of separate kernels with materialised
+ * intermediates (it allocates on first use and is not meant for graph capture).  FUSED with n <= 64 allocates no device memory and is
  * graph-capturable.  Outside stream capture the call records a completion
  * event on the stream for dpf_result_release.  A plan must not be in two
  * executions at once.  *out receives a result handle that is readable after

@@ -146,6 +146,103 @@ struct DevAcc { int32_t nterms; int32_t pad; DevTerm t[kMaxTerms]; };
 
 enum : uint32_t { ST_CORRUPT = 1u, ST_CAPACITY = 2u, ST_UNSUPPORTED = 4u, ST_DUPLICATE = 8u };
 
+// The plan as the lean kernel reads it (fused_lean.hip): values carried as
+// 32-bit offsets u = value - ref.
+constexpr int kLeanTiles = 16;    // mini blocks whose headers a wave prepares at a time
+constexpr int kLeanEnts = kMaxPreds + kMaxSlots;
+// Copies of an LDS group table: at most 8, in 8 KB.  (6 groups: the 24M-row
+// summary took 204 us with 4 copies, 166 with 8, 164 with 16; the 60M-row filter
+// 216, 215 and 224, 266 with 32.)
+constexpr int kMaxLeanLog2r = 3;
+constexpr int kLeanAggBytes = 8 * 1024;
+
+struct LeanEnt {            // one column as an atom or a value slot reads it
+    const uint32_t* words;
+    const uint32_t* woff;
+    const int64_t* base;
+    const int64_t* dmin;
+    int64_t lo, hi;         // atom: its range (lo: the excluded value); else lo: u = decoded value - lo
+                            // (with a dictionary: u is the code, lo 0)
+    uint32_t nwords;
+    int32_t enc;
+    int32_t kind;           // atom: PK_*
+    int32_t maxw;           // widest mini block of the column, at most 25
+    // Staging area of the column's packed words, for one mini block: its place
+    // in the wave's, whether this entry copies them (0: an entry before it with
+    // the same column does; 2: for a later one too), its bytes.
+    uint32_t stage_off, stage_copy, stage_sz;
+    uint32_t pad;
+};
+static_assert(sizeof(LeanEnt) == 80, "copied to LDS in 16-byte units");
+struct LeanMore {           // what only the rarer paths need of an entry
+    const uint32_t* words;
+    const uint32_t* woff;
+    const int64_t* base;
+    const int64_t* dmin;
+    int64_t ref;
+    const int64_t* dict;    // value slot of a DICT column's values: u = dict[code] - dref
+    int64_t dref;
+    uint32_t nwords;
+    int32_t enc;
+    int32_t ndict;
+    int32_t col;            // index into DevQuery::cols
+};
+struct LeanTerm {           // factor mul * u + c (slot < 0: c)
+    int32_t slot;
+    int32_t mk;             // mul when it is 1 or -1, else 0
+    int64_t mul, c;
+};
+struct LeanAcc {
+    int32_t nterms;
+    // 0: u + c; 1: every factor in [0, 2^24); 2: general; 3: as 1, and the
+    // factors but the last are those of the accumulator before it
+    int32_t cls;
+    LeanTerm t[kMaxTerms];
+};
+struct LeanPlan {
+    int32_t ok;             // the plan qualifies
+    int32_t nents;          // entries: atoms, then value slots
+    int32_t load0;          // first value slot's entry
+    int32_t log2r;          // copies of the LDS group table: up to 2^log2r
+    int32_t stage_bytes;    // a wave's staging area for the packed words of one mini block
+    int32_t dicts;          // value slots that hold a DICT column's values: bits
+    // Direct group tables: the key slots (bits), each with its largest value
+    // and its stride.
+    int32_t keys;
+    uint32_t key_last[kMaxSlots];
+    uint32_t key_stride[kMaxSlots];
+    alignas(16) LeanEnt ents[kLeanEnts];
+    LeanMore more[kLeanEnts];
+    LeanAcc accs[kMaxAccs];
+    // In the LDS group table, a sum of a slot's plain values u + c is kept as
+    // the sum of u (slot s in accumulator plain_acc[s], where plain has bit s)
+    // and c times the group's rows is added when the table leaves LDS (fold).
+    // The other accumulators are prod_acc[0 .. nprod).
+    int32_t plain;
+    int32_t nprod;
+    int32_t plain_acc[kMaxSlots];
+    int32_t prod_acc[kMaxAccs];
+    int64_t fold[kMaxAccs];
+};
+
+// Queued rows of a wave: fewer than 256 and those of a mini block of fewer than
+// kDenseMin (fused_lean.hip).
+constexpr int kLeanQueue = 384;
+// A wave's LDS: header records, queue, staging area.
+__host__ __device__ constexpr size_t lean_wave_bytes(int ents, int stage) {
+    return (size_t)ents * kLeanTiles * 16 + kLeanQueue * 2 + (size_t)stage;
+}
+// Guided work items (lean kernel, one plan of mb mini blocks to scan): XCD
+// x's range starts at guided_start and is cut into the returned number of
+// items, the first nbig of big mini blocks, the rest of small.
+__host__ __device__ inline int guided_start(int mb, int x) { return (int)((int64_t)mb * x / kXcds); }
+__host__ __device__ inline int guided_items(int mb, int big, int small, int x, int& r0, int& nbig) {
+    r0 = guided_start(mb, x);
+    const int len = guided_start(mb, x + 1) - r0;
+    nbig = len / 8 * 7 / big;
+    return nbig + (len - nbig * big + small - 1) / small;
+}
+
 struct DevQuery {
     int64_t nrows;
     int32_t nmb;
@@ -196,6 +293,7 @@ struct DevQuery {
     const int32_t* live;
     int32_t nlive;
     int32_t prune_mb;
+    LeanPlan lean;
 };
 
 // Bytes of a plan's group table: the accumulators, and the keys of a hash
@@ -220,6 +318,12 @@ struct BatchArgs {
     int32_t str_stage;    // per-wave string staging present (2: some plan has an FSST atom)
     int32_t pend_stage;   // per-wave survivor queue present (some plan has a fact predicate or a probe)
     int32_t agg_hash;     // some plan aggregates into a hash group table
+    int32_t lean_ents;    // lean kernel: most entries of a plan
+    int32_t lean_stage;   // a wave's staging bytes
+    int32_t lean_group;   // mini blocks staged together: 4, 2 or 1
+    int32_t lean_log2r;   // copies of an LDS group table: at most 2^lean_log2r
+    int32_t guided_mb;    // lean kernel: a lone plan's mini blocks (of its surviving blocks; else 0) and its small items' size
+    int32_t small_mb;
 };
 
 // Hash build over a dimension table (optionally joined: the rows must find
@@ -264,6 +368,8 @@ struct HashTableArgs {
 hipError_t launch_fused(const BatchArgs& a, int waves, int grid, size_t lds_bytes, hipStream_t s);
 hipError_t launch_fused_str(const BatchArgs& a, int waves, int grid, size_t lds_bytes, hipStream_t s);
 hipError_t launch_fused_fsst(const BatchArgs& a, int waves, int grid, size_t lds_bytes, hipStream_t s);
+// The lean kernel: every plan of the batch has lean.ok.
+hipError_t launch_lean(const BatchArgs& a, int waves, int grid, size_t lds_bytes, hipStream_t s);
 // Per-wave LDS the fused kernel needs (survivor queue, string row offsets).
 size_t fused_wave_area_bytes(bool str, bool pend);
 hipError_t launch_hash_count(const HashBuildArgs* d_args, int grid, hipStream_t s);

@@ -303,6 +303,7 @@ dpf_status encode_column(const dpf_column_src& src, int32_t enc, int32_t chunk_r
     uint64_t total = 0;
     for (int64_t m = 0; m < nmb; ++m) {
         c.woff[m] = (uint32_t)total;
+        c.max_width = std::max<int32_t>(c.max_width, width[m]);
         total += 8u * width[m];
         if (total > 0xFFFFFFF0ull - kWordPad) {
             *err = "column exceeds 2^32 packed words";

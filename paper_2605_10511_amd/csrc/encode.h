@@ -32,6 +32,7 @@ struct ColView {
 struct HostColumn {
     int32_t type = 0, enc = 0, chunk_rows = 0;
     int64_t nrows = 0, nmb = 0, nchunks = 0;
+    int32_t max_width = 0;  // widest mini block, bits
     int64_t minv = 0, maxv = 0;
     std::vector<int64_t> base;
     std::vector<uint32_t> woff;

@@ -342,12 +342,8 @@ __device__ unsigned long long flush_lds_agg(CQ& Q, uint8_t* smem_shared, unsigne
     return sink;
 }
 
-// Load a plan's LDS-resident dimension tables and clear its LDS group table.
-__device__ void load_lds_state(CQ& Q, uint8_t* smem_shared, uint32_t* str_tab) {
-    if (Q.npreds > 0 && threadIdx.x < 32) {
-        CP& PL = Q.preds[Q.npreds - 1];
-        if (PL.kind == PK_STR && PL.tab_rot) str_tab[threadIdx.x] = PL.tab[threadIdx.x];
-    }
+// Load a plan's LDS-resident dimension tables.
+__device__ __forceinline__ void load_lds_tables(CQ& Q, uint8_t* smem_shared) {
     for (int j = 0; j < Q.nprobes; ++j) {
         CH& h = Q.probes[j].h;
         if (h.bits_lds_off >= 0) {
@@ -367,6 +363,16 @@ __device__ void load_lds_state(CQ& Q, uint8_t* smem_shared, uint32_t* str_tab) {
         uint4* dst = reinterpret_cast<uint4*>(smem_shared + h.lds_off);
         for (uint32_t e = threadIdx.x; e < h.bytes / 16u; e += blockDim.x) dst[e] = ld4(src, e);
     }
+}
+
+// The plan's whole LDS state: string table, dimension tables, a cleared group
+// table.
+__device__ void load_lds_state(CQ& Q, uint8_t* smem_shared, uint32_t* str_tab) {
+    if (Q.npreds > 0 && threadIdx.x < 32) {
+        CP& PL = Q.preds[Q.npreds - 1];
+        if (PL.kind == PK_STR && PL.tab_rot) str_tab[threadIdx.x] = PL.tab[threadIdx.x];
+    }
+    load_lds_tables(Q, smem_shared);
     if (Q.agg_lds) {
         const int64_t n = Q.ngroups * Q.nacc;
         unsigned long long* T = reinterpret_cast<unsigned long long*>(smem_shared + Q.agg_lds_off);
@@ -410,6 +416,44 @@ __device__ __forceinline__ bool finish_last(const BatchArgs& a, int home) {
     __threadfence();
     const uint32_t nx = gridDim.x < (uint32_t)kXcds ? gridDim.x : (uint32_t)kXcds;
     return atomicAdd(ctr(a, 2 * kXcds), 1u) == nx - 1u;
+}
+
+// Mini blocks [mb0, mb1) of a plan's work item t: a slice of the plan, or,
+// after chunk pruning, a slice of one surviving block.
+__device__ __forceinline__ void item_range(const BatchArgs& a, CQ& Q, int t, int& mb0, int& mb1) {
+    if (Q.live) {
+        const int ipc = (Q.prune_mb + a.mb_per_item - 1) / a.mb_per_item;  // items per block
+        const int j = t / ipc;
+        const int blk = ro(Q.live)[j];
+        mb0 = blk * Q.prune_mb + (t - j * ipc) * a.mb_per_item;
+        mb1 = min(min(mb0 + a.mb_per_item, (blk + 1) * Q.prune_mb), Q.nmb);
+    } else {
+        mb0 = t * a.mb_per_item;
+        mb1 = min(mb0 + a.mb_per_item, Q.nmb);
+    }
+}
+
+// The end of a launch, entered by every workgroup once its global effects
+// have been performed: the last one in emits the plans' group tables and
+// resets the work queue.
+__device__ __forceinline__ void finish_launch(const BatchArgs& a, int32_t* ctrl, int home, int nw, int wave, int lane) {
+    if (threadIdx.x == 0) ctrl[1] = finish_last(a, home) ? 1 : 0;
+    __syncthreads();
+    if (!ctrl[1]) return;
+    __threadfence();
+    // One wave a plan where the batch has more plans than the workgroup waves
+    // (each plan's copy is mostly one wait for memory), else all threads on
+    // each plan in turn.  Larger tables are left to emit_kernel.
+    const bool by_wave = a.nq >= nw;
+    for (int qi = by_wave ? wave : 0; qi < a.nq; qi += by_wave ? nw : 1) {
+        CQ& Q = *ro(a.q[qi]);
+        if (!Q.emit_copy) continue;
+        emit_table(Q, reinterpret_cast<unsigned long long*>(a.agg[qi]), a.status[qi],
+                   by_wave ? lane : (int)threadIdx.x, by_wave ? kWave : (int)blockDim.x);
+    }
+    if (threadIdx.x < 2 * kXcds + 1)  // every other workgroup has left: reset for the next launch
+        __hip_atomic_store(ctr(a, threadIdx.x), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __threadfence_system();
 }
 
 // ---------------------------------------------------------------------------
@@ -479,20 +523,8 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(kStr
             cur = qi;
             direct |= Q.agg_lds == 0;
         }
-        // The item's mini blocks: a slice of the plan, or, after chunk
-        // pruning, a slice of one surviving block.
-        const int t = item - a.item_start[qi];
         int mb0, mb1;
-        if (Q.live) {
-            const int ipc = (Q.prune_mb + a.mb_per_item - 1) / a.mb_per_item;  // items per block
-            const int j = t / ipc;
-            const int blk = ro(Q.live)[j];
-            mb0 = blk * Q.prune_mb + (t - j * ipc) * a.mb_per_item;
-            mb1 = min(min(mb0 + a.mb_per_item, (blk + 1) * Q.prune_mb), Q.nmb);
-        } else {
-            mb0 = t * a.mb_per_item;
-            mb1 = min(mb0 + a.mb_per_item, Q.nmb);
-        }
+        item_range(a, Q, item - a.item_start[qi], mb0, mb1);
         if (Q.npreds == 0 && Q.nprobes > 0) {
             semi_tiles<kHash>(Q, shared_area, gagg, W, mb0 + wave, mb1, nw, lane, npend, ok_hdr);
         } else if (kStr == 2 && Q.fs_pred >= 0) {
@@ -534,23 +566,7 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(kStr
     if (direct) __threadfence();
     if (sink == ~0ull) ctrl[3] = 1;  // consumes every returned value
     __syncthreads();
-    if (threadIdx.x == 0) ctrl[1] = finish_last(a, home) ? 1 : 0;
-    __syncthreads();
-    if (!ctrl[1]) return;
-    __threadfence();
-    // One wave a plan where the batch has more plans than the workgroup waves
-    // (each plan's copy is mostly one wait for memory), else all threads on
-    // each plan in turn.  Larger tables are left to emit_kernel.
-    const bool by_wave = a.nq >= nw;
-    for (int qi = by_wave ? wave : 0; qi < a.nq; qi += by_wave ? nw : 1) {
-        CQ& Q = *ro(a.q[qi]);
-        if (!Q.emit_copy) continue;
-        emit_table(Q, reinterpret_cast<unsigned long long*>(a.agg[qi]), a.status[qi],
-                   by_wave ? lane : (int)threadIdx.x, by_wave ? kWave : (int)blockDim.x);
-    }
-    if (threadIdx.x < 2 * kXcds + 1)  // every other workgroup has left: reset for the next launch
-        __hip_atomic_store(ctr(a, threadIdx.x), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __threadfence_system();
+    finish_launch(a, ctrl, home, nw, wave, lane);
 }
 
 // Two instantiations per string mode, each mode compiled in a source file of

@@ -174,6 +174,7 @@ struct dpf_plan_s {
     int64_t nblocks = 0, nlive = 0;            // chunk pruning: blocks in all, blocks scanned
     int32_t lds_budget = -2;
     int32_t naggs_out = 0;
+    int32_t nacc_listed = 1;  // the row count and every SUM and AVG, equal ones included
     bool issued = false;
     // The descriptor, block list and zeroed workspace go to the device on the
     // context's upload stream from this pinned staging copy; executions wait
@@ -923,6 +924,12 @@ constexpr int64_t kAggLdsMax = 16 * 1024;
 constexpr int64_t kDefaultMbPerItem = 64;  // 16,384 rows
 constexpr int kTargetWavesPerCU = 24;       // string stage: 6 waves per SIMD (its register occupancy)
 constexpr int kTargetWavesPerCUNoStr = 24;  // without it: also 6 waves per SIMD
+constexpr int kLeanWavesPerCU = 16;         // lean kernel: 4 waves per SIMD (its registers)
+// Rows that a mixed batch's plans for the lean kernel must scan to be launched
+// by themselves: over 2M rows the lean kernel gains 4 to 45 us, more than a
+// launch costs (6 us), over 1M rows of a selective scan nothing.  (64 queries, half of them
+// with probes: 923 us in one launch, 646 in two.)
+constexpr int64_t kSplitRows = 2 << 20;
 
 // Places the plan's dimension tables and group table in the workgroup's LDS
 // shared area within budget; fills lds offsets and lds_shared.
@@ -985,6 +992,13 @@ void assign_lds(dpf_plan p, int32_t budget) {
     p->lds_budget = budget;
 }
 
+// Shared-area bytes of the plan in the lean kernel, whose LDS group table has
+// copies and a spare group (the table comes last in the area).
+int32_t lean_shared(const DevQuery& q, int32_t log2r) {
+    if (!q.agg_lds) return q.lds_shared;
+    return q.agg_lds_off + (int32_t)align_up((size_t)(((q.ngroups + 1) * q.nacc * 8) << std::min(q.lean.log2r, log2r)), 16);
+}
+
 // Largest |mul * x + add| over x in [lo, hi].
 __int128 term_bound(int64_t mul, int64_t add, int64_t lo, int64_t hi) {
     __int128 a = (__int128)mul * lo + add, b = (__int128)mul * hi + add;
@@ -998,6 +1012,138 @@ void free_frag(dpf_plan p) {
     p->frag_allocs.clear();
     p->frag_bytes = 0;
     p->frag_ready = false;
+}
+}  // namespace
+
+namespace {
+// The plan in the lean kernel's form (LeanPlan), when it qualifies: integer
+// atoms only; no probes (the star query over 6M fact rows took 75 us there, 63
+// in the general kernel; over 48M 174 and 183); every value slot's range below
+// 2^32 (values are carried as 32-bit offsets from the range's start, exact
+// modulo 2^64 once widened); no slot twice as a key.
+void fill_lean(const dpf_plan_desc* desc, DevQuery& q, const std::vector<int64_t>& lo, const std::vector<int64_t>& hi) {
+    LeanPlan& L = q.lean;
+    L.ok = 0;
+    if (q.has_str || q.nprobes > 0) return;
+    auto narrow = [](int64_t a, int64_t b) { return b < a || (unsigned __int128)((__int128)b - a) < (uint64_t(1) << 32); };
+    for (size_t s = 0; s < lo.size(); ++s)
+        if (!narrow(lo[s], hi[s])) return;
+    auto view = [&](int col, int64_t ref) {
+        const DevCol& c = q.cols[col];
+        LeanMore e{};
+        e.words = c.words;
+        e.woff = c.woff;
+        e.base = c.base;
+        e.dmin = c.dmin;
+        e.ref = ref;
+        e.nwords = c.nwords;
+        e.enc = c.enc;
+        e.col = col;
+        return e;
+    };
+    int n = 0;
+    for (int p = 0; p < q.npreds; ++p) {
+        const DevPred& P = q.preds[p];
+        L.ents[n].kind = P.kind;
+        L.ents[n].lo = P.lo;
+        L.ents[n].hi = P.hi;
+        L.more[n++] = view(P.col, 0);
+    }
+    L.load0 = n;
+    for (int l = 0; l < q.nloads; ++l) {
+        const DevLoad& d = q.loads[l];
+        LeanMore e = view(d.col, d.dict_val ? 0 : lo[(size_t)l]);
+        if (d.dict_val) {
+            e.dict = q.cols[d.col].dict;
+            e.ndict = q.cols[d.col].ndict;
+            e.dref = lo[(size_t)l];
+            L.dicts |= 1 << l;
+        }
+        L.ents[n].lo = e.ref;
+        L.more[n++] = e;
+    }
+    L.nents = n;
+    // Staging: 32 bytes a bit of width and mini block (those wider than 25
+    // bits are decoded another way), 16 more for the last row's dwords.  Of the
+    // atoms the first three are staged, of all entries the first 16; a column
+    // that is both is staged once.
+    for (int e = 0; e < n; ++e) {
+        LeanEnt& E = L.ents[e];
+        E.maxw = std::min(desc->cols[L.more[e].col]->host.max_width, 25);
+        E.stage_sz = (uint32_t)(32 * E.maxw);
+        E.stage_off = E.stage_copy = 0;
+        const bool atom = e < q.npreds;
+        if (e >= 16 || (atom && e >= 3)) continue;
+        int f = 0;
+        while (f < e && (L.more[f].col != L.more[e].col || L.ents[f].stage_copy == 0)) ++f;
+        if (f < e && !atom) {
+            L.ents[f].stage_copy = 2;
+            E.stage_off = L.ents[f].stage_off;
+            continue;
+        }
+        E.stage_off = (uint32_t)L.stage_bytes;
+        E.stage_copy = 1;
+        L.stage_bytes += (int32_t)E.stage_sz + 16;
+    }
+    for (int e = 0; e < n; ++e) {
+        L.ents[e].words = L.more[e].words;
+        L.ents[e].woff = L.more[e].woff;
+        L.ents[e].base = L.more[e].base;
+        L.ents[e].dmin = L.more[e].dmin;
+        L.ents[e].nwords = L.more[e].nwords;
+        L.ents[e].enc = L.more[e].enc;
+    }
+    // (the same slot twice as a key: the general kernel)
+    for (int k = 0; k < q.nkeys; ++k) {
+        const DevKey& K = q.keys[k];
+        if ((L.keys >> K.slot) & 1) return;
+        L.keys |= 1 << K.slot;
+        L.key_last[K.slot] = (uint32_t)(K.card - 1);
+        L.key_stride[K.slot] = (uint32_t)K.stride;
+    }
+    auto same = [](const DevTerm& x, const DevTerm& y) { return x.slot == y.slot && x.mul == y.mul && x.add == y.add; };
+    for (int a = 1; a < q.nacc; ++a) {
+        const DevAcc& A = q.accs[a];
+        LeanAcc& B = L.accs[a];
+        B.nterms = A.nterms;
+        bool small = true;
+        for (int t = 0; t < A.nterms; ++t) {
+            const DevTerm& T = A.t[t];
+            LeanTerm& U = B.t[t];
+            U.slot = T.slot;
+            U.mul = T.mul;
+            U.mk = T.mul == 1 ? 1 : T.mul == -1 ? -1 : 0;
+            U.c = T.slot < 0 ? T.add : (int64_t)((uint64_t)T.mul * (uint64_t)lo[(size_t)T.slot] + (uint64_t)T.add);
+            __int128 v0 = T.add, v1 = T.add;
+            if (T.slot >= 0) {
+                v0 += (__int128)T.mul * lo[(size_t)T.slot];
+                v1 += (__int128)T.mul * hi[(size_t)T.slot];
+            }
+            const __int128 top = (__int128)1 << 24;
+            small = small && v0 >= 0 && v1 >= 0 && v0 < top && v1 < top;
+        }
+        const bool plain = A.nterms == 1 && (A.t[0].slot < 0 || A.t[0].mul == 1);
+        B.cls = plain ? 0 : small ? 1 : 2;
+        // one factor more than the accumulator before it: (a product of two
+        // 24-bit factors is below 2^48, as the third step wants it)
+        if (B.cls == 1 && A.nterms == 3 && a > 1 && L.accs[a - 1].cls == 1 && q.accs[a - 1].nterms == 2 &&
+            same(A.t[0], q.accs[a - 1].t[0]) && same(A.t[1], q.accs[a - 1].t[1]))
+            B.cls = 3;
+        const int s = A.t[0].slot;
+        if (plain && s >= 0 && !((L.plain >> s) & 1)) {
+            L.plain |= 1 << s;
+            L.plain_acc[s] = a;
+            L.fold[a] = B.t[0].c;
+        } else {
+            L.prod_acc[L.nprod++] = a;
+        }
+    }
+    // Copies of the LDS group table (and one spare group for rows that are
+    // masked out), a power of two.
+    L.log2r = 0;
+    const int64_t one = (q.ngroups + 1) * q.nacc * 8;
+    while (L.log2r < kMaxLeanLog2r && (one << (L.log2r + 1)) <= kLeanAggBytes) ++L.log2r;
+    L.ok = 1;
 }
 }  // namespace
 
@@ -1144,7 +1290,7 @@ extern "C" dpf_status dpf_plan_build(dpf_ctx ctx, const dpf_plan_desc* desc, dpf
     }
 
     // value slots: (fact column, as value) or (probe, payload)
-    struct SlotKey { int kind, a, b; };
+    struct SlotKey { int kind, a, b; int64_t lo, hi; };
     std::vector<SlotKey> slots;
     auto slot_of = [&](const dpf_ref& r, bool as_value, int* slot, int64_t* lo, int64_t* hi, const int64_t** dict) -> dpf_status {
         SlotKey k{};
@@ -1171,6 +1317,8 @@ extern "C" dpf_status dpf_plan_build(dpf_ctx ctx, const dpf_plan_desc* desc, dpf
         for (size_t s = 0; s < slots.size(); ++s)
             if (slots[s].kind == k.kind && slots[s].a == k.a && slots[s].b == k.b) { *slot = (int)s; return DPF_OK; }
         if ((int)slots.size() >= kMaxSlots) return fail(DPF_ERR_UNSUPPORTED, "more than 8 distinct key/term values");
+        k.lo = *lo;
+        k.hi = *hi;
         slots.push_back(k);
         *slot = (int)slots.size() - 1;
         return DPF_OK;
@@ -1228,7 +1376,7 @@ extern "C" dpf_status dpf_plan_build(dpf_ctx ctx, const dpf_plan_desc* desc, dpf
         if (ag.op == DPF_AGG_COUNT) { p->outcols.push_back({0, 0}); continue; }
         if (ag.op != DPF_AGG_SUM && ag.op != DPF_AGG_AVG) return bail(fail(DPF_ERR_INVALID_ARG, "unknown aggregate"));
         if (ag.nterms < 1 || ag.nterms > kMaxTerms) return bail(fail(DPF_ERR_INVALID_ARG, "1..3 terms"));
-        if (q.nacc >= kMaxAccs) return bail(fail(DPF_ERR_UNSUPPORTED, "more than 11 sums"));
+        if (p->nacc_listed >= kMaxAccs) return bail(fail(DPF_ERR_UNSUPPORTED, "more than 11 sums"));
         DevAcc& A = q.accs[q.nacc];
         A.nterms = ag.nterms;
         __int128 bound = 1;
@@ -1257,9 +1405,19 @@ extern "C" dpf_status dpf_plan_build(dpf_ctx ctx, const dpf_plan_desc* desc, dpf
         }
         if (bound * (__int128)std::max<int64_t>(nrows, 1) > lim)
             return bail(fail(DPF_ERR_OVERFLOW, "an aggregate sum can exceed int64 over this table"));
-        p->outcols.push_back({q.nacc, 1});
+        // a sum that the plan already has (SUM(x) beside AVG(x)) is kept once
+        int at = 1;
+        auto same = [](const DevAcc& x, const DevAcc& y) {
+            bool eq = x.nterms == y.nterms;
+            for (int t = 0; eq && t < x.nterms; ++t)
+                eq = x.t[t].slot == y.t[t].slot && x.t[t].mul == y.t[t].mul && x.t[t].add == y.t[t].add;
+            return eq;
+        };
+        while (at < q.nacc && !same(q.accs[at], A)) ++at;
+        p->outcols.push_back({at, 1});
         if (ag.op == DPF_AGG_AVG) p->outcols.push_back({0, 0});
-        q.nacc++;
+        if (at == q.nacc) q.nacc++;
+        p->nacc_listed++;
     }
     // Renumber slots so fact-column loads take slots 0..nloads-1 (the kernel
     // writes those with compile-time indices) and payloads the ones after.
@@ -1279,10 +1437,16 @@ extern "C" dpf_status dpf_plan_build(dpf_ctx ctx, const dpf_plan_desc* desc, dpf
         remap[s] = next;
         q.probes[slots[s].a].pay_slot[slots[s].b] = next++;
     }
+    std::vector<int64_t> slot_lo(slots.size()), slot_hi(slots.size());
+    for (size_t s = 0; s < slots.size(); ++s) {
+        slot_lo[(size_t)remap[s]] = slots[s].lo;
+        slot_hi[(size_t)remap[s]] = slots[s].hi;
+    }
     for (int k = 0; k < q.nkeys; ++k) q.keys[k].slot = remap[q.keys[k].slot];
     for (int a = 1; a < q.nacc; ++a)
         for (int t = 0; t < q.accs[a].nterms; ++t)
             if (q.accs[a].t[t].slot >= 0) q.accs[a].t[t].slot = remap[q.accs[a].t[t].slot];
+    fill_lean(desc, q, slot_lo, slot_hi);
     q.emit_copy = !q.agg_hash && q.ngroups * q.nacc <= kEmitEntries;
     assign_lds(p, -1);
 
@@ -1503,6 +1667,150 @@ dpf_status check_fused_opts(int32_t n, const dpf_exec_opts& o) {
 }
 
 // One launch of the persistent fused kernel over n plans.
+// One launch of the general or the lean kernel over the n plans idx names.
+dpf_status launch_fused_part(dpf_ctx ctx, int32_t n, const int32_t* idx, const dpf_plan* all, const dpf_exec_opts& o,
+                             const FusedWorkspace& ws, hipStream_t s) {
+    dpf_plan plans[kMaxBatch];
+    for (int i = 0; i < n; ++i) plans[i] = all[idx[i]];
+    BatchArgs a;
+    std::memset(&a, 0, sizeof a);
+    a.nq = n;
+    a.counters = ws.counters;
+    bool str = false, pend = false, fsst = false;
+    int32_t shared = 0;
+    int64_t total_mb = 0;
+    for (int i = 0; i < n; ++i) {
+        const DevQuery& q = plans[i]->hq;
+        a.q[i] = plans[i]->dq;
+        a.agg[i] = ws.agg[idx[i]];
+        a.status[i] = ws.status[idx[i]];
+        str |= q.has_str != 0;
+        fsst |= q.fs_pred >= 0;
+        pend |= q.npreds > 0 || q.nprobes > 0;
+        a.agg_hash |= q.agg_hash;
+        shared = std::max(shared, q.lds_shared);
+        total_mb += q.live ? std::min<int64_t>(q.nmb, (int64_t)q.nlive * q.prune_mb) : q.nmb;
+    }
+    a.lds_shared = (int32_t)align_up((size_t)shared, 16);
+    a.str_stage = fsst ? 2 : str ? 1 : 0;
+    a.pend_stage = pend;
+    bool lean = true;
+    for (int i = 0; i < n; ++i) lean &= plans[i]->hq.lean.ok != 0;
+    auto lds_for = [&](int w) {
+        if (lean)
+            return kLdsCtrlBytes + (size_t)a.lds_shared + (size_t)a.lean_ents * sizeof(LeanEnt) +
+                   (size_t)w * lean_wave_bytes(a.lean_ents, a.lean_stage);
+        return kLdsHeadBytes + (size_t)a.lds_shared + (size_t)w * fused_wave_area_bytes(str, pend);
+    };
+    // Waves per workgroup: large LDS-resident dimension tables are shared
+    // by more waves (one copy per workgroup); otherwise small workgroups.
+    int waves = o.waves_per_wg;
+    const int lds_cu = 160 * 1024;
+    if (lean) {
+        // The most waves a CU first (up to the registers' limit), then the most
+        // mini blocks staged together, then the most copies of a group table,
+        // then the smallest workgroup.
+        const int32_t general_shared = a.lds_shared;
+        int32_t stage1 = 0, lds_tables[kMaxLeanLog2r + 1] = {};
+        for (int i = 0; i < n; ++i) {
+            const DevQuery& q = plans[i]->hq;
+            a.lean_ents = std::max(a.lean_ents, q.lean.nents);
+            stage1 = std::max(stage1, q.lean.stage_bytes);
+            for (int r = 0; r <= kMaxLeanLog2r; ++r) lds_tables[r] = std::max(lds_tables[r], lean_shared(q, r));
+        }
+        auto set_lean = [&](int group, int log2r) {
+            a.lds_shared = (int32_t)align_up((size_t)lds_tables[log2r], 16);
+            a.lean_stage = stage1 * group;
+            a.lean_group = group;
+            a.lean_log2r = log2r;
+        };
+        int best = 0, best_group = 0, best_log2r = 0, best_w = 0;
+        for (int w : {4, 8, 16})
+            for (int group : {4, 2, 1})
+                for (int log2r = kMaxLeanLog2r; log2r >= 0; --log2r) {
+                    if (o.waves_per_wg != 0 && w != o.waves_per_wg) continue;
+                    set_lean(group, log2r);
+                    const int64_t bytes = (int64_t)lds_for(w);
+                    if (bytes > ctx->lds_per_block) continue;
+                    const int resident = std::min<int>(kLeanWavesPerCU / w, (int)(lds_cu / bytes)) * w;
+                    const int score = resident * 1000 + group * 100 + log2r * 10 + (w == 4);
+                    if (score <= best) continue;
+                    best = score, best_w = w, best_group = group, best_log2r = log2r;
+                }
+        if (best) {
+            set_lean(best_group, best_log2r);
+            waves = best_w;
+        } else {  // its LDS does not fit beside the dimension tables
+            lean = false;
+            a.lds_shared = general_shared;
+        }
+    }
+    if (waves == 0) {
+        waves = 4;
+        if (a.lds_shared >= 32 * 1024)
+            for (int w : {16, 8})
+                if ((int64_t)lds_for(w) <= ctx->lds_per_block) { waves = w; break; }
+    }
+    if (waves != 4 && waves != 8 && waves != 16) return fail(DPF_ERR_INVALID_ARG, "waves_per_wg: 4, 8 or 16");
+    const size_t lds = lds_for(waves);
+    if ((int64_t)lds > ctx->lds_per_block)
+        return fail(DPF_ERR_UNSUPPORTED, "plan LDS needs exceed the workgroup limit; lower lds_hash_bytes");
+    int wg = o.wg_per_cu;
+    if (wg <= 0)
+        wg = std::max(1, (lean ? kLeanWavesPerCU : str ? kTargetWavesPerCU : kTargetWavesPerCUNoStr) / waves);
+    wg = std::max(1, std::min<int>(wg, (int)(lds_cu / lds)));
+    int grid = std::max(1, ctx->ncu * wg);
+    if (o.max_workgroups > 0) grid = std::min(grid, o.max_workgroups);
+    // Work-item size: the caller's, else 64 mini blocks (16,384 rows),
+    // shrunk for small batches so that every workgroup gets about three
+    // items, but never below one mini block per wave.
+    int64_t mb_per_item = o.rows_per_item / kMB;
+    if (mb_per_item == 0) {
+        const int64_t most = lean ? (int64_t)kLeanTiles * waves : kDefaultMbPerItem;  // one header step a wave
+        mb_per_item = std::min<int64_t>(most, (total_mb + 3LL * grid - 1) / (3LL * grid));
+        mb_per_item = std::max<int64_t>(mb_per_item, waves);  // total_mb is 0 when every block is pruned
+        // a pruned plan's items are slices of its blocks: even slices
+        for (int i = 0; i < n && !(lean && n == 1); ++i)
+            if (plans[i]->hq.live) {
+                const int64_t u = plans[i]->hq.prune_mb, k = (u + mb_per_item - 1) / mb_per_item;
+                mb_per_item = (u + k - 1) / k;
+                break;
+            }
+        mb_per_item = std::max<int64_t>(mb_per_item, waves);
+        const DevQuery& q0 = plans[0]->hq;
+        const int64_t scan_mb = q0.live ? (int64_t)q0.nlive * q0.prune_mb : q0.nmb;
+        if (lean && n == 1 && scan_mb > 0) {
+            // whole runs of mini blocks a wave, the last eighth in items half the size (lean_claim)
+            mb_per_item = (mb_per_item + waves - 1) / waves * waves;
+            a.guided_mb = (int32_t)scan_mb;
+            a.small_mb = (int32_t)std::max<int64_t>(waves, mb_per_item / 2 / waves * waves);
+        }
+    }
+    a.mb_per_item = (int32_t)mb_per_item;
+    int64_t items = 0;
+    for (int i = 0; i < n; ++i) {
+        a.item_start[i] = (int32_t)items;
+        const DevQuery& q = plans[i]->hq;
+        items += q.live ? (int64_t)q.nlive * ((q.prune_mb + mb_per_item - 1) / mb_per_item)
+                        : (q.nmb + mb_per_item - 1) / mb_per_item;
+    }
+    if (a.guided_mb) {
+        items = 0;
+        for (int x = 0; x < kXcds; ++x) {
+            int r0, nbig;
+            items += guided_items(a.guided_mb, a.mb_per_item, a.small_mb, x, r0, nbig);
+        }
+    }
+    if (items > INT32_MAX) return fail(DPF_ERR_UNSUPPORTED, "too many work items; raise rows_per_item");
+    a.item_start[n] = (int32_t)items;
+    // no more workgroups than items: an idle workgroup still claims and signs off
+    grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, items));
+    if (lean) HIP_TRY(launch_lean(a, waves, grid, lds, s));
+    else HIP_TRY(launch_fused(a, waves, grid, lds - kLdsStrTabBytes, s));  // the string table is static LDS
+    ctx->launches++;
+    return DPF_OK;
+}
+
 dpf_status launch_fused_batch(dpf_ctx ctx, int32_t n, const dpf_plan* plans, const dpf_exec_opts& o,
                               const FusedWorkspace& ws, hipStream_t s) {
     // LDS placement follows the requested budget (re-uploads the
@@ -1518,79 +1826,30 @@ dpf_status launch_fused_batch(dpf_ctx ctx, int32_t n, const dpf_plan* plans, con
             HIP_TRY(hipMemcpyAsync(p->dq, &p->hq, sizeof(DevQuery), hipMemcpyHostToDevice, s));
         }
     }
-    BatchArgs a;
-    std::memset(&a, 0, sizeof a);
-    a.nq = n;
-    a.counters = ws.counters;
-    bool str = false, pend = false, fsst = false;
-    int32_t shared = 0;
-    int64_t total_mb = 0;
+    // The lean kernel takes a batch whose plans all qualify.  Of a mixed one it
+    // takes the plans that do, in a launch of their own, once they scan
+    // kSplitRows rows.
+    int32_t idx[kMaxBatch];
+    int64_t lean_rows = 0;
+    int nlean = 0;
     for (int i = 0; i < n; ++i) {
         const DevQuery& q = plans[i]->hq;
-        a.q[i] = plans[i]->dq;
-        a.agg[i] = ws.agg[i];
-        a.status[i] = ws.status[i];
-        str |= q.has_str != 0;
-        fsst |= q.fs_pred >= 0;
-        pend |= q.npreds > 0 || q.nprobes > 0;
-        a.agg_hash |= q.agg_hash;
-        shared = std::max(shared, q.lds_shared);
-        total_mb += q.live ? std::min<int64_t>(q.nmb, (int64_t)q.nlive * q.prune_mb) : q.nmb;
+        if (!q.lean.ok) continue;
+        lean_rows += q.live ? (int64_t)q.nlive * q.prune_mb * kMB : q.nrows;
+        nlean++;
     }
-    a.lds_shared = (int32_t)align_up((size_t)shared, 16);
-    a.str_stage = fsst ? 2 : str ? 1 : 0;
-    a.pend_stage = pend;
-    auto lds_for = [&](int w) { return kLdsHeadBytes + (size_t)a.lds_shared + (size_t)w * fused_wave_area_bytes(str, pend); };
-    // Waves per workgroup: large LDS-resident dimension tables are shared
-    // by more waves (one copy per workgroup); otherwise small workgroups.
-    int waves = o.waves_per_wg;
-    if (waves == 0) {
-        waves = 4;
-        if (a.lds_shared >= 32 * 1024)
-            for (int w : {16, 8})
-                if ((int64_t)lds_for(w) <= ctx->lds_per_block) { waves = w; break; }
+    const bool split = nlean > 0 && nlean < n && lean_rows >= kSplitRows;
+    if (ws.clear_bytes) {
+        HIP_TRY(launch_fill_i32((int32_t*)ws.clear, 0, (int64_t)(ws.clear_bytes / 4), s));
+        ctx->launches++;
     }
-    if (waves != 4 && waves != 8 && waves != 16) return fail(DPF_ERR_INVALID_ARG, "waves_per_wg: 4, 8 or 16");
-    const size_t lds = lds_for(waves);
-    if ((int64_t)lds > ctx->lds_per_block)
-        return fail(DPF_ERR_UNSUPPORTED, "plan LDS needs exceed the workgroup limit; lower lds_hash_bytes");
-    const int lds_cu = 160 * 1024;
-    int wg = o.wg_per_cu;
-    if (wg <= 0) wg = std::max(1, (str ? kTargetWavesPerCU : kTargetWavesPerCUNoStr) / waves);
-    wg = std::max(1, std::min<int>(wg, (int)(lds_cu / lds)));
-    int grid = std::max(1, ctx->ncu * wg);
-    if (o.max_workgroups > 0) grid = std::min(grid, o.max_workgroups);
-    // Work-item size: the caller's, else 64 mini blocks (16,384 rows),
-    // shrunk for small batches so that every workgroup gets about three
-    // items, but never below one mini block per wave.
-    int64_t mb_per_item = o.rows_per_item / kMB;
-    if (mb_per_item == 0) {
-        mb_per_item = std::min<int64_t>(kDefaultMbPerItem, (total_mb + 3LL * grid - 1) / (3LL * grid));
-        mb_per_item = std::max<int64_t>(mb_per_item, waves);  // total_mb is 0 when every block is pruned
-        // a pruned plan's items are slices of its blocks: even slices
+    for (int part = split ? 0 : 1; part < 2; ++part) {
+        int k = 0;
         for (int i = 0; i < n; ++i)
-            if (plans[i]->hq.live) {
-                const int64_t u = plans[i]->hq.prune_mb, k = (u + mb_per_item - 1) / mb_per_item;
-                mb_per_item = (u + k - 1) / k;
-                break;
-            }
-        mb_per_item = std::max<int64_t>(mb_per_item, waves);
+            if (!split || (plans[i]->hq.lean.ok != 0) == (part == 0)) idx[k++] = i;
+        const dpf_status st = launch_fused_part(ctx, k, idx, plans, o, ws, s);
+        if (st != DPF_OK) return st;
     }
-    a.mb_per_item = (int32_t)mb_per_item;
-    int64_t items = 0;
-    for (int i = 0; i < n; ++i) {
-        a.item_start[i] = (int32_t)items;
-        const DevQuery& q = plans[i]->hq;
-        items += q.live ? (int64_t)q.nlive * ((q.prune_mb + mb_per_item - 1) / mb_per_item)
-                        : (q.nmb + mb_per_item - 1) / mb_per_item;
-    }
-    if (items > INT32_MAX) return fail(DPF_ERR_UNSUPPORTED, "too many work items; raise rows_per_item");
-    a.item_start[n] = (int32_t)items;
-    // no more workgroups than items: an idle workgroup still claims and signs off
-    grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, items));
-    if (ws.clear_bytes) HIP_TRY(launch_fill_i32((int32_t*)ws.clear, 0, (int64_t)(ws.clear_bytes / 4), s));
-    HIP_TRY(launch_fused(a, waves, grid, lds - kLdsStrTabBytes, s));  // the table is static LDS
-    ctx->launches += ws.clear_bytes ? 2 : 1;
     for (int i = 0; i < n; ++i) {
         if (plans[i]->hq.emit_copy) continue;
         HIP_TRY(launch_emit(plans[i]->dq, plans[i]->hq, ws.agg[i], ws.status[i], s));
@@ -1685,7 +1944,8 @@ extern "C" dpf_status dpf_execute_noalloc(dpf_ctx ctx, int32_t n, const dpf_plan
     ws.counters = (uint32_t*)ctx->scratch;
     for (int i = 0; i < n; ++i) {
         const DevQuery& q = plans[i]->hq;
-        const size_t agg_bytes = agg_table_bytes(q);
+        // (room for every listed sum, as documented, equal ones included)
+        const size_t agg_bytes = (size_t)q.ngroups * (size_t)(plans[i]->nacc_listed + (q.agg_hash ? 1 : 0)) * 8;
         if (agg_bytes > kStaticScratchBytes) off = kStaticScratchBytes + 1;
         if (off > kStaticScratchBytes) break;
         ws.status[i] = (uint32_t*)(ctx->scratch + off);

@@ -1,0 +1,154 @@
+"""The fused kernel for scans whose values fit 32 bits (fused_lean.hip): row
+counts around a mini block (256), a staged group (1,024) and a header step
+(4,096 rows); survivor counts around the dense threshold and the queue's 256;
+every width and encoding that takes a path of its own; direct tables in LDS, in
+device memory and hash tables; pruned blocks; batches that are split by kernel.
+Results against the CPU oracle, exact (every value is an integer)."""
+import numpy as np
+import pytest
+
+import oracle
+from tests import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    from paper_2605_10511_amd import dpf
+    assert torch.cuda.is_available()
+    return dpf.Context(0)
+
+
+ENC = {"day": "DELTA", "step": "DELTA", "ramp": "DELTA", "dic": "DICT", "dkey": "DICT"}
+
+
+def _table(n: int, seed: int) -> dict:
+    rng = np.random.default_rng(seed)
+    i = np.arange(n, dtype=np.int64)
+    return {
+        "a": rng.integers(0, 1000, n, dtype=np.int32),           # the filter: a < s keeps s rows in 1000
+        "b": rng.integers(-50, 50, n, dtype=np.int32),
+        "c": np.where(i // 256 % 3 == 0, 7, rng.integers(0, 1 << 24, n)).astype(np.int32),  # all of some mini blocks
+        "w0": np.full(n, -12345, dtype=np.int32),
+        "w1": rng.integers(0, 2, n, dtype=np.int32),
+        "w25": rng.integers(0, 1 << 25, n, dtype=np.int32),
+        "w26": rng.integers(-(1 << 25), 1 << 25, n, dtype=np.int32),
+        "w32": rng.integers(-(1 << 31), 1 << 31, n, dtype=np.int64),
+        "wide": rng.integers(0, 1 << 40, n, dtype=np.int64),     # not the lean kernel's
+        "far": rng.integers((1 << 40), (1 << 40) + 900, n, dtype=np.int64),
+        "day": (i // 700).astype(np.int32),                      # DELTA of width 0 and 1
+        "step": (i * 3).astype(np.int32),                        # DELTA of width 0
+        "ramp": np.cumsum(rng.integers(0, 40, n)).astype(np.int64) % (1 << 31),  # DELTA, wider
+        "dic": rng.choice(np.array([-70000, 3, 5, 1 << 20], dtype=np.int32), n),
+        "dkey": rng.choice(np.array([11, 12, 400, 90000], dtype=np.int32), n),
+        "k6": rng.integers(-3, 3, n, dtype=np.int32),
+        "k9k": rng.integers(0, 9000, n, dtype=np.int32),
+        "h20": (i * 7919 % (1 << 20)).astype(np.int32),
+    }
+
+
+def _s(col, mul=1, add=0):
+    return {"ref": {"col": col}, "mul": mul, "add": add}
+
+
+def _spec(filters, group_by, aggs):
+    return {"fact": "t", "filters": filters, "probes": [], "group_by": [{"col": c} for c in group_by], "aggs": aggs}
+
+
+def _lt(s):
+    return {"col": "a", "op": "LT", "value": s}
+
+
+SUMS = {
+    "plain": [{"op": "COUNT"}] + [{"op": "SUM", "terms": [_s(c)]} for c in ("w0", "w1", "w25", "w26", "far")],
+    "wide": [{"op": "SUM", "terms": [_s("w32")]}, {"op": "SUM", "terms": [_s("dic")]}, {"op": "AVG", "terms": [_s("ramp")]},
+             {"op": "SUM", "terms": [_s("step", -2, 9)]}],
+    "products": [{"op": "SUM", "terms": [_s("a"), _s("b", -1, 60)]},
+                 {"op": "SUM", "terms": [_s("a"), _s("b", -1, 60), _s("w1", 1, 3)]},
+                 {"op": "SUM", "terms": [_s("b"), _s("b", -3, 2), _s("w26")]},
+                 {"op": "SUM", "terms": [_s("a")]}, {"op": "AVG", "terms": [_s("a")]}, {"op": "SUM", "terms": [_s("a")]},
+                 {"op": "SUM", "terms": [{"const": 5}]}],
+    "general": [{"op": "SUM", "terms": [_s("wide")]}],
+}
+FILTERS = {
+    "none": [], "nothing": [_lt(-1)], "all": [_lt(1000)], "sparse": [_lt(4)], "staged": [_lt(63)],
+    "below": [_lt(365)], "dense": [_lt(400)],
+    "ne": [_lt(300), {"col": "b", "op": "NE", "value": 7}, {"col": "c", "op": "NE", "value": 7}],
+    "in": [{"col": "k6", "op": "IN", "values": [-3, 0, 2]}, {"col": "c", "op": "BETWEEN", "lo": 5, "hi": 1 << 23}],
+    "wide": [{"col": "w26", "op": "GT", "value": 0}, {"col": "w32", "op": "LT", "value": 1 << 30}, {"col": "far", "op": "GE", "value": (1 << 40) + 200}],
+    "many": [_lt(900), {"col": "b", "op": "GE", "value": -45}, {"col": "w1", "op": "LE", "value": 1},
+             {"col": "w25", "op": "GT", "value": 1000}, {"col": "k6", "op": "NE", "value": 1}],
+    "delta": [{"col": "ramp", "op": "GE", "value": 300}, {"col": "day", "op": "LE", "value": 11}],
+}
+GROUPS = {"one": [], "six": ["k6"], "dict": ["dkey", "w1"], "day": ["day"], "hbm": ["k9k"], "hash": ["h20", "k9k"]}
+ROWS = [1, 255, 256, 257, 1023, 1025, 4095, 4097, 3 * 4096 + 77]
+
+
+# every filter with every row count in turn, sums and groups rotating
+@pytest.mark.parametrize("filt", sorted(FILTERS))
+@pytest.mark.parametrize("group", sorted(GROUPS))
+def test_lean_forms(ctx, filt, group):
+    k = sorted(FILTERS).index(filt) + 5 * sorted(GROUPS).index(group)
+    for r, sums in enumerate(SUMS):
+        n = ROWS[(k + 2 * r) % len(ROWS)]
+        t = _table(n, 100 * k + r)
+        spec = _spec(FILTERS[filt], GROUPS[group], SUMS[sums])
+        db = G.make_db(ctx, {"t": t}, {"t": ENC}, chunk_rows=4096)
+        want = oracle.run(spec, {"t": t})
+        for mode, kw in (("FUSED", {}), ("FUSED", {"waves_per_wg": 16, "max_workgroups": 1}), ("FRAGMENTED", {})):
+            G.say(f"lean {filt} {group} {sums} rows={n} {mode} {kw}")
+            G.assert_same(G.run_gpu(db, spec, mode=mode, **kw), want, f"{filt} {group} {sums} {mode} {kw}")
+
+
+def test_lean_pruned_and_large(ctx):
+    """Blocks left out by their zone maps, runs of mini blocks that cross block
+    edges, and enough rows for several items a workgroup."""
+    n = 1_500_007
+    t = _table(n, 3)
+    db = G.make_db(ctx, {"t": t}, {"t": ENC}, chunk_rows=2048)
+    day = [{"col": "day", "op": "BETWEEN", "lo": 300, "hi": 1700}]
+    for filters, group in ((day, ["k6"]), (day + [_lt(30)], ["day"]), (day + [{"col": "step", "op": "GE", "value": 2_000_000}], []),
+                           ([_lt(125)], ["k6"]), ([], ["day"]), ([{"col": "day", "op": "GT", "value": 1 << 20}], [])):
+        spec = _spec(filters, group, SUMS["products"])
+        G.say("lean pruned", filters, group)
+        G.assert_same(G.run_gpu(db, spec), oracle.run(spec, {"t": t}), f"{filters} {group}")
+
+
+def test_lean_split_batch_and_replay(ctx):
+    """A batch of plans for both kernels, large enough for two launches: once as
+    it is, in static scratch, and replayed from a graph with work in between."""
+    import torch
+    from paper_2605_10511_amd import dpf
+    n = 1_100_000
+    t = _table(n, 4)
+    dim = {"k": np.arange(0, 9000, 2, dtype=np.int32), "p": (np.arange(0, 9000, 2) % 5).astype(np.int32)}
+    tables = {"t": t, "d": dim}
+    probe = {"fact": "t", "filters": [_lt(500)],
+             "probes": [{"fk": "k9k", "dim": "d", "key": "k", "filters": [], "payloads": ["p"]}],
+             "group_by": [{"probe": 0, "payload": 0}], "aggs": [{"op": "COUNT"}, {"op": "SUM", "terms": [_s("a")]}]}
+    specs = [_spec([_lt(125)], ["k6"], SUMS["plain"]), probe, _spec([], ["dkey"], SUMS["products"]),
+             _spec([_lt(999)], [], SUMS["general"]), _spec([_lt(2)], ["day"], SUMS["wide"])]
+    db = G.make_db(ctx, tables, {"t": ENC})
+    want = [oracle.run(s, tables) for s in specs]
+    plans = [db.plan(s) for s in specs]
+    for name, run in (("execute", dpf.execute), ("noalloc", dpf.execute_noalloc)):
+        G.say("lean split", name)
+        res = run(ctx, plans)
+        torch.cuda.synchronize()
+        for i in range(len(plans)):
+            G.assert_same(res.get(i), want[i], f"{name} {i}")
+        res.release()
+    s = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        res = dpf.execute(ctx, plans, stream=s)
+    for k in range(3):
+        G.say("lean split replay", k)
+        g.replay()
+        torch.cuda.synchronize()
+        for i in range(len(plans)):
+            G.assert_same(res.get(i), want[i], f"replay {k} {i}")
+        torch.zeros(1 << 20, device="cuda").sum().item()
+    res.release()
