@@ -232,17 +232,6 @@ constexpr int kLeanQueue = 384;
 __host__ __device__ constexpr size_t lean_wave_bytes(int ents, int stage) {
     return (size_t)ents * kLeanTiles * 16 + kLeanQueue * 2 + (size_t)stage;
 }
-// Guided work items (lean kernel, one plan of mb mini blocks to scan): XCD
-// x's range starts at guided_start and is cut into the returned number of
-// items, the first nbig of big mini blocks, the rest of small.
-__host__ __device__ inline int guided_start(int mb, int x) { return (int)((int64_t)mb * x / kXcds); }
-__host__ __device__ inline int guided_items(int mb, int big, int small, int x, int& r0, int& nbig) {
-    r0 = guided_start(mb, x);
-    const int len = guided_start(mb, x + 1) - r0;
-    nbig = len / 8 * 7 / big;
-    return nbig + (len - nbig * big + small - 1) / small;
-}
-
 struct DevQuery {
     int64_t nrows;
     int32_t nmb;
@@ -322,9 +311,24 @@ struct BatchArgs {
     int32_t lean_stage;   // a wave's staging bytes
     int32_t lean_group;   // mini blocks staged together: 4, 2 or 1
     int32_t lean_log2r;   // copies of an LDS group table: at most 2^lean_log2r
-    int32_t guided_mb;    // lean kernel: a lone plan's mini blocks (of its surviving blocks; else 0) and its small items' size
+    // A lone plan's guided items (else guided_mb 0): its mini blocks (of its
+    // surviving blocks), the large items' share of them in eighths, the small
+    // items' mini blocks (the large: mb_per_item).
+    int32_t guided_mb;
+    int32_t big_share;
     int32_t small_mb;
 };
+
+// Guided work items of XCD x: its mini blocks start at r0 and make the
+// returned number of items, the first nbig of mb_per_item, the rest of
+// small_mb mini blocks.
+__host__ __device__ inline int guided_start(int mb, int x) { return (int)((int64_t)mb * x / kXcds); }
+__host__ __device__ inline int guided_items(const BatchArgs& a, int x, int& r0, int& nbig) {
+    r0 = guided_start(a.guided_mb, x);
+    const int len = guided_start(a.guided_mb, x + 1) - r0;
+    nbig = (int)((uint32_t)(len / 8 * a.big_share) / (uint32_t)a.mb_per_item);
+    return nbig + (int)((uint32_t)(len - nbig * a.mb_per_item + a.small_mb - 1) / (uint32_t)a.small_mb);
+}
 
 // Hash build over a dimension table (optionally joined: the rows must find
 // their foreign keys in the tables of sub[], probed from device memory).

@@ -35,7 +35,6 @@ namespace {
 using CLC = const DPF_AS_CONST LeanMore;
 using CLA = const DPF_AS_CONST LeanAcc;
 using CLT = const DPF_AS_CONST LeanTerm;
-typedef uint32_t u32_a1 __attribute__((aligned(1)));
 #define DPF_AS_GLOBAL __attribute__((address_space(1)))
 #define DPF_AS_LDS __attribute__((address_space(3)))
 typedef DPF_AS_GLOBAL unsigned long long gu64;
@@ -839,30 +838,6 @@ __device__ unsigned long long lean_flush_agg(CQ& Q, uint8_t* smem_shared, unsign
     return sink;
 }
 
-// Claims of a lone plan: each XCD's eighth of the mini blocks is cut into items
-// of mb_per_item for its first seven eighths and of half as many after that, so
-// that the workgroups end together (24M-row summary: 185 us with one size, 179
-// so).
-__device__ __forceinline__ int lean_claim(const BatchArgs& a, int home, uint32_t& drained, int& mb0, int& mb1) {
-    for (int k = 0; k < kXcds; ++k) {
-        const int x = (home + k) & (kXcds - 1);
-        if ((drained >> x) & 1u) continue;
-        int r0, nbig;
-        const uint32_t n = (uint32_t)guided_items(a.guided_mb, a.mb_per_item, a.small_mb, x, r0, nbig);
-        uint32_t* head = ctr(a, x);
-        uint32_t j = n;
-        if (k == 0 || __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n) j = atomicAdd(head, 1u);
-        if (j < n) {
-            const int r1 = guided_start(a.guided_mb, x + 1);
-            mb0 = r0 + ((int)j < nbig ? (int)j * a.mb_per_item : nbig * a.mb_per_item + ((int)j - nbig) * a.small_mb);
-            mb1 = min(mb0 + ((int)j < nbig ? a.mb_per_item : a.small_mb), r1);
-            return 0;
-        }
-        drained |= 1u << x;
-    }
-    return -1;
-}
-
 // ---------------------------------------------------------------------------
 // The kernel: work items as in fused_kernel, an item's mini blocks cut into
 // one run a wave.
@@ -893,20 +868,10 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(4, 8
     unsigned long long sink = 0;
     int cur = -1;
     bool ok_hdr = true, values = true;
-    for (;;) {
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            if (a.guided_mb) {
-                int mb0 = 0, mb1 = 0;
-                ctrl[0] = lean_claim(a, home, drained, mb0, mb1);
-                ctrl[4] = mb0;
-                ctrl[5] = mb1;
-            } else {
-                ctrl[0] = claim_item(a, home, drained, total_items);
-            }
-        }
-        __syncthreads();
-        const int item = uniform_i32(ctrl[0]);
+    const bool guided = a.guided_mb != 0;
+    for (bool first = true;; first = false) {
+        int item = 0, mb0 = 0, mb1 = 0;
+        next_item<true>(a, ctrl, home, drained, first, wave, lane, total_items, item, mb0, mb1);
         int qi = 0;
         if (item >= 0) {
             while (qi + 1 < a.nq && a.item_start[qi + 1] <= item) ++qi;
@@ -935,18 +900,12 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(4, 8
             __syncthreads();
             cur = qi;
         }
-        int mb0, mb1;
-        if (a.guided_mb) {
-            mb0 = uniform_i32(ctrl[4]);
-            mb1 = uniform_i32(ctrl[5]);
-        } else {
-            item_range(a, Q, item - a.item_start[qi], mb0, mb1);
-        }
+        if (!guided) item_range(a, Q, item - a.item_start[qi], mb0, mb1);
         const int per = (mb1 - mb0 + nw - 1) / nw;
         const int t1 = min(mb1, mb0 + (wave + 1) * per);
         // (a guided item of a pruned plan counts the surviving blocks' mini
         // blocks: its run may lie in several of them)
-        const bool blocks = a.guided_mb && Q.live;
+        const bool blocks = guided && Q.live;
         for (int v = mb0 + wave * per; v < t1;) {
             int s0 = v, s1 = t1;
             if (blocks) {

@@ -921,7 +921,7 @@ namespace {
 constexpr int32_t kDefaultLdsHash = 72 * 1024;
 constexpr int64_t kAggLdsMax = 16 * 1024;
 
-constexpr int64_t kDefaultMbPerItem = 64;  // 16,384 rows
+constexpr int64_t kMbPerItem = 128, kMbPerStrItem = 64;  // 32,768 and 16,384 rows
 constexpr int kTargetWavesPerCU = 24;       // string stage: 6 waves per SIMD (its register occupancy)
 constexpr int kTargetWavesPerCUNoStr = 24;  // without it: also 6 waves per SIMD
 constexpr int kLeanWavesPerCU = 16;         // lean kernel: 4 waves per SIMD (its registers)
@@ -1745,11 +1745,20 @@ dpf_status launch_fused_part(dpf_ctx ctx, int32_t n, const int32_t* idx, const d
             a.lds_shared = general_shared;
         }
     }
+    // Waves a workgroup: as many a CU as fit beside the dimension tables (one
+    // copy a workgroup), in the smallest workgroups.  With string atoms 4, where
+    // those fit: larger ones wait longer at an item's end (6M FSST comments 154
+    // us with 4, 190 with 8).
+    const int target = lean ? kLeanWavesPerCU : str ? kTargetWavesPerCU : kTargetWavesPerCUNoStr;
     if (waves == 0) {
         waves = 4;
-        if (a.lds_shared >= 32 * 1024)
-            for (int w : {16, 8})
-                if ((int64_t)lds_for(w) <= ctx->lds_per_block) { waves = w; break; }
+        int best = 0;
+        for (int w : {4, 8, 16}) {
+            const int64_t bytes = (int64_t)lds_for(w);
+            if (bytes > ctx->lds_per_block || (str && best)) continue;
+            const int resident = std::min<int>(target / w, (int)(lds_cu / bytes)) * w;
+            if (resident > best) best = resident, waves = w;
+        }
     }
     if (waves != 4 && waves != 8 && waves != 16) return fail(DPF_ERR_INVALID_ARG, "waves_per_wg: 4, 8 or 16");
     const size_t lds = lds_for(waves);
@@ -1757,34 +1766,48 @@ dpf_status launch_fused_part(dpf_ctx ctx, int32_t n, const int32_t* idx, const d
         return fail(DPF_ERR_UNSUPPORTED, "plan LDS needs exceed the workgroup limit; lower lds_hash_bytes");
     int wg = o.wg_per_cu;
     if (wg <= 0)
-        wg = std::max(1, (lean ? kLeanWavesPerCU : str ? kTargetWavesPerCU : kTargetWavesPerCUNoStr) / waves);
+        wg = std::max(1, target / waves);
     wg = std::max(1, std::min<int>(wg, (int)(lds_cu / lds)));
     int grid = std::max(1, ctx->ncu * wg);
     if (o.max_workgroups > 0) grid = std::min(grid, o.max_workgroups);
-    // Work-item size: the caller's, else 64 mini blocks (16,384 rows),
-    // shrunk for small batches so that every workgroup gets about three
-    // items, but never below one mini block per wave.
+    // Work-item size: the caller's, else whole runs of the workgroup's waves:
+    // for the lean kernel and batches about three items a workgroup, for a
+    // lone plan of the general kernel one, or the fewest equal ones up to
+    // kMbPerItem.  (At an item's end its waves wait for the slowest, then for the
+    // claim.  Three items and one: 5M comments 113 and 87 us, 6M FSST comments
+    // 157 and 113, 16M comments 183 and 154; 48M-row star join with items of 64
+    // and 128 mini blocks 184 and 175, of 256 206.)  Mini blocks of strings differ
+    // in what they take: a share above kMbPerStrItem goes in items of that size
+    // (60M rows in items of 128 and 64: VARLEN 537 and 408 us, FSST 702 and 633).
     int64_t mb_per_item = o.rows_per_item / kMB;
     if (mb_per_item == 0) {
-        const int64_t most = lean ? (int64_t)kLeanTiles * waves : kDefaultMbPerItem;  // one header step a wave
-        mb_per_item = std::min<int64_t>(most, (total_mb + 3LL * grid - 1) / (3LL * grid));
-        mb_per_item = std::max<int64_t>(mb_per_item, waves);  // total_mb is 0 when every block is pruned
-        // a pruned plan's items are slices of its blocks: even slices
-        for (int i = 0; i < n && !(lean && n == 1); ++i)
-            if (plans[i]->hq.live) {
-                const int64_t u = plans[i]->hq.prune_mb, k = (u + mb_per_item - 1) / mb_per_item;
-                mb_per_item = (u + k - 1) / k;
-                break;
-            }
-        mb_per_item = std::max<int64_t>(mb_per_item, waves);
+        auto whole = [&](int64_t mb) { return std::max<int64_t>((mb + waves - 1) / waves * waves, waves); };
+        const int64_t most = lean ? (int64_t)kLeanTiles * waves : kMbPerItem;  // lean: one header step a wave
         const DevQuery& q0 = plans[0]->hq;
         const int64_t scan_mb = q0.live ? (int64_t)q0.nlive * q0.prune_mb : q0.nmb;
-        if (lean && n == 1 && scan_mb > 0) {
-            // whole runs of mini blocks a wave, the last eighth in items half the size (lean_claim)
-            mb_per_item = (mb_per_item + waves - 1) / waves * waves;
-            a.guided_mb = (int32_t)scan_mb;
-            a.small_mb = (int32_t)std::max<int64_t>(waves, mb_per_item / 2 / waves * waves);
+        const bool guided = n == 1 && scan_mb > 0 && (lean || (str && !fsst));
+        const int64_t share = (total_mb + grid - 1) / grid;  // a workgroup's
+        if (lean || n > 1) {
+            mb_per_item = whole(std::min<int64_t>(most, (share + 2) / 3));
+        } else if (str && share > kMbPerStrItem) {
+            mb_per_item = kMbPerStrItem;
+        } else {
+            const int64_t k = std::max<int64_t>((share + most - 1) / most, 1);
+            mb_per_item = whole((share + k - 1) / k);
         }
+        if (guided) {
+            const bool one = !lean && share <= kMbPerStrItem;  // a workgroup's one item
+            a.guided_mb = (int32_t)scan_mb;
+            a.big_share = one ? 8 : 7;
+            a.small_mb = (int32_t)(one ? waves : whole(mb_per_item / (lean ? 2 : 4)));
+        }
+        // a pruned plan's items are slices of its blocks: even slices
+        for (int i = 0; i < n && !guided; ++i)
+            if (plans[i]->hq.live) {
+                const int64_t u = plans[i]->hq.prune_mb, k = (u + mb_per_item - 1) / mb_per_item;
+                mb_per_item = whole((u + k - 1) / k);
+                break;
+            }
     }
     a.mb_per_item = (int32_t)mb_per_item;
     int64_t items = 0;
@@ -1798,7 +1821,7 @@ dpf_status launch_fused_part(dpf_ctx ctx, int32_t n, const int32_t* idx, const d
         items = 0;
         for (int x = 0; x < kXcds; ++x) {
             int r0, nbig;
-            items += guided_items(a.guided_mb, a.mb_per_item, a.small_mb, x, r0, nbig);
+            items += guided_items(a, x, r0, nbig);
         }
     }
     if (items > INT32_MAX) return fail(DPF_ERR_UNSUPPORTED, "too many work items; raise rows_per_item");

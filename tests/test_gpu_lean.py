@@ -152,3 +152,28 @@ def test_lean_split_batch_and_replay(ctx):
             G.assert_same(res.get(i), want[i], f"replay {k} {i}")
         torch.zeros(1 << 20, device="cuda").sum().item()
     res.release()
+
+
+# grids of one workgroup (it takes every item from all eight ranges), of three,
+# and the default; items of the default size and of one mini block a wave
+@pytest.mark.parametrize("max_wg, rows_per_item", [(1, 0), (3, 0), (9, 1024), (0, 1024), (0, 0)])
+def test_items_taken_once(ctx, max_wg, rows_per_item):
+    """Work items of a lone plan: every kernel (32-bit scan, string, semi-join,
+    FSST) over a table with pruned blocks and a ragged end."""
+    from tests.conftest import to_strings
+    n = 40_000 + 77
+    t = _table(n, 8)
+    rng = np.random.default_rng(8)
+    words = [b"alpha", b"beta", b"gamma", b"delta", b"alphabeta"]
+    text = to_strings([b" ".join(words[j] for j in rng.integers(0, 5, 4)) for _ in range(n)])
+    tables = {"t": {**t, "s": text, "z": text}, "d": {"k": np.arange(0, 9000, 3, dtype=np.int32)}}
+    db = G.make_db(ctx, tables, {"t": {**ENC, "z": "FSST"}}, chunk_rows=2048)
+    day = [{"col": "day", "op": "BETWEEN", "lo": 9, "hi": 47}]
+    like = {"op": "STR_CONTAINS_SEQ", "s1": b"alpha", "s2": b"gamma"}
+    semi = {**_spec([], ["k6"], SUMS["plain"]), "probes": [{"fk": "k9k", "dim": "d", "key": "k", "filters": [], "payloads": []}]}
+    for name, spec in (("scan", _spec(day, ["k6"], SUMS["plain"])), ("like", _spec(day + [{"col": "s", **like}], ["k6"], SUMS["plain"])),
+                       ("like all", _spec([{"col": "s", **like}], [], SUMS["plain"])), ("semi", semi),
+                       ("fsst", _spec(day + [{"col": "z", **like}], ["k6"], SUMS["plain"]))):
+        G.say(f"items {name} max_wg={max_wg} rows_per_item={rows_per_item}")
+        got = G.run_gpu(db, spec, max_workgroups=max_wg, rows_per_item=rows_per_item)
+        G.assert_same(got, oracle.run(spec, tables), name)
