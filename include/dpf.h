@@ -356,8 +356,8 @@ typedef struct {
     int32_t mode;
     int32_t wg_per_cu;       /* FUSED: workgroups per compute unit (0 = auto)          */
     int32_t rows_per_item;   /* FUSED: rows per work item, multiple of 256 (0 = auto:   */
-                             /* at most 16384, about three items per workgroup; even   */
-                             /* slices of a pruned plan's blocks)                       */
+                             /* at most 32768, one to three items per workgroup; in    */
+                             /* batches even slices of a pruned plan's blocks)          */
     int32_t lds_hash_bytes;  /* FUSED: LDS budget for dimension tables (-1 = auto:     */
                              /* 72 KB, none for batches of more than 8 plans)          */
     int32_t waves_per_wg;    /* FUSED: 4, 8 or 16 waves per workgroup (0 = auto)       */
@@ -372,8 +372,8 @@ typedef struct {
  * others scan 2M rows or more; a plan whose group table is hashed or exceeds
  * 8,192 accumulators has its records written by a small launch more);
  * FRAGMENTED runs each plan as a sequence of separate kernels with materialised
- * intermediates (it allocates on first use and is not meant for graph capture).  FUSED with n <= 64 allocates no device memory and is
- * graph-capturable.  Outside stream capture the call records a completion
+ * intermediates (it allocates on first use and is not meant for graph capture).
+ * FUSED with n <= 64 allocates no device memory and is graph-capturable.  Outside stream capture the call records a completion
  * event on the stream for dpf_result_release.  A plan must not be in two
  * executions at once.  *out receives a result handle that is readable after
  * the stream has synchronised. */

@@ -384,9 +384,8 @@ __device__ void load_lds_state(CQ& Q, uint8_t* smem_shared, uint32_t* str_tab) {
 // Work queue.  Workgroup i runs on XCD i % 8 (round-robin dispatch), and each
 // XCD has its own L2, so a single queue head would serialise every claim of
 // the grid on one device-coherent atomic.  Instead the items are split into
-// eight contiguous ranges with one head each: a workgroup claims from its
-// XCD's range, then steals from the others, skipping a drained range after a
-// plain load of its head.  Completion counts per XCD and then across XCDs.
+// eight contiguous ranges with one head each: a workgroup takes items of
+// its XCD's range, then of the others.  Completion counts per XCD and then across XCDs.
 // The dispatch rule only affects speed: any workgroup may take any item.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t* ctr(const BatchArgs& a, int i) { return a.counters + i * kCounterStride; }

@@ -921,7 +921,8 @@ namespace {
 constexpr int32_t kDefaultLdsHash = 72 * 1024;
 constexpr int64_t kAggLdsMax = 16 * 1024;
 
-constexpr int64_t kMbPerItem = 128, kMbPerStrItem = 64;  // 32,768 and 16,384 rows
+constexpr int64_t kMbPerItem = 64;       // 16,384 rows
+constexpr int64_t kMbPerLoneItem = 128;  // a lone plan without string atoms
 constexpr int kTargetWavesPerCU = 24;       // string stage: 6 waves per SIMD (its register occupancy)
 constexpr int kTargetWavesPerCUNoStr = 24;  // without it: also 6 waves per SIMD
 constexpr int kLeanWavesPerCU = 16;         // lean kernel: 4 waves per SIMD (its registers)
@@ -1773,30 +1774,30 @@ dpf_status launch_fused_part(dpf_ctx ctx, int32_t n, const int32_t* idx, const d
     // Work-item size: the caller's, else whole runs of the workgroup's waves:
     // for the lean kernel and batches about three items a workgroup, for a
     // lone plan of the general kernel one, or the fewest equal ones up to
-    // kMbPerItem.  (At an item's end its waves wait for the slowest, then for the
+    // kMbPerLoneItem.  (At an item's end its waves wait for the slowest, then for the
     // claim.  Three items and one: 5M comments 113 and 87 us, 6M FSST comments
     // 157 and 113, 16M comments 183 and 154; 48M-row star join with items of 64
     // and 128 mini blocks 184 and 175, of 256 206.)  Mini blocks of strings differ
-    // in what they take: a share above kMbPerStrItem goes in items of that size
+    // in what they take: a share above kMbPerItem goes in items of that size
     // (60M rows in items of 128 and 64: VARLEN 537 and 408 us, FSST 702 and 633).
     int64_t mb_per_item = o.rows_per_item / kMB;
     if (mb_per_item == 0) {
         auto whole = [&](int64_t mb) { return std::max<int64_t>((mb + waves - 1) / waves * waves, waves); };
-        const int64_t most = lean ? (int64_t)kLeanTiles * waves : kMbPerItem;  // lean: one header step a wave
+        const int64_t most = lean ? (int64_t)kLeanTiles * waves : n > 1 || str ? kMbPerItem : kMbPerLoneItem;  // lean: one header step a wave
         const DevQuery& q0 = plans[0]->hq;
         const int64_t scan_mb = q0.live ? (int64_t)q0.nlive * q0.prune_mb : q0.nmb;
         const bool guided = n == 1 && scan_mb > 0 && (lean || (str && !fsst));
         const int64_t share = (total_mb + grid - 1) / grid;  // a workgroup's
         if (lean || n > 1) {
             mb_per_item = whole(std::min<int64_t>(most, (share + 2) / 3));
-        } else if (str && share > kMbPerStrItem) {
-            mb_per_item = kMbPerStrItem;
+        } else if (str && share > kMbPerItem) {
+            mb_per_item = kMbPerItem;
         } else {
             const int64_t k = std::max<int64_t>((share + most - 1) / most, 1);
             mb_per_item = whole((share + k - 1) / k);
         }
         if (guided) {
-            const bool one = !lean && share <= kMbPerStrItem;  // a workgroup's one item
+            const bool one = !lean && share <= kMbPerItem;  // a workgroup's one item
             a.guided_mb = (int32_t)scan_mb;
             a.big_share = one ? 8 : 7;
             a.small_mb = (int32_t)(one ? waves : whole(mb_per_item / (lean ? 2 : 4)));
