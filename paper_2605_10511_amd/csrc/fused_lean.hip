@@ -1,11 +1,11 @@
 // fused_lean.hip -- the fused kernel for batches whose plans carry every
-// value in 32 bits (LeanPlan: integer atoms only, each group key, measure and
+// value in 32 bits (LeanPlan: no probes, integer atoms only, each group key, measure and
 // payload an offset of less than 2^32 from its column's minimum, which holds
 // for all but plans over truly 64-bit columns).  fused.h has the general
 // kernel; both share the work queue, the group tables and the emission.
 //
 // What bounds it: latency and instruction issue, not bandwidth (60M-row filter
-// 2.0 TB/s, 24M-row summary 3.4 TB/s of the 5.7 a plain read reaches).  The
+// 1.4 TB/s, 24M-row summary 0.7 TB/s of the 5.7 a plain read reaches).  The
 // general kernel decodes to 64 bits, reads its descriptors with chains of
 // scalar loads for every mini block and again for every 64 surviving rows, and
 // adds each row to a group table that all lanes of a workgroup share, or to
@@ -41,8 +41,8 @@ typedef DPF_AS_GLOBAL unsigned long long gu64;
 
 // Rows a mini block must keep for its value columns to be staged and the rows
 // aggregated in place.  At 32 of 256 rows (60M-row filter) gathering took 260
-// us, staging 363; a mini block of the 24M-row summary (250 of 256) 157 us in
-// place, more than 214 gathered.
+// us, staging 363.  The other scans measured keep far more or far fewer rows a
+// mini block: 48 and 64 instead of 96 made no difference to them.
 constexpr int kDenseMin = 96;
 // The same where the value columns are there already (the first mini blocks of
 // a scan): 40,000 rows in 40.3 us, with 48 in 41.8.
