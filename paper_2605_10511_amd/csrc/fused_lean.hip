@@ -150,7 +150,8 @@ __device__ __forceinline__ uint32_t lean_setup(CQ& Q, const LeanWave& W, int m0,
                 y = ne ? 0xFFFFFFFEu : h32 - l32;
                 meta |= (all ? kHdrAll : 0u) | (zero ? kHdrNone : 0u) | (gen ? kHdrGeneral : 0u);
             } else {
-                meta |= delta ? (b > 1 ? kHdrGeneral : kHdrDelta) : b > maxw ? kHdrGeneral : 0u;
+                // (a bad header stays kHdrGeneral alone: decode_dense and lean_at report it)
+                meta |= delta ? (!hok || b > 1 ? kHdrGeneral : kHdrDelta) : b > maxw ? kHdrGeneral : 0u;
                 x = (uint32_t)(uint64_t)base[h] - (uint32_t)(uint64_t)plo;
                 y = (uint32_t)(uint64_t)dmin[h];
             }

@@ -177,3 +177,40 @@ def test_items_taken_once(ctx, max_wg, rows_per_item):
         G.say(f"items {name} max_wg={max_wg} rows_per_item={rows_per_item}")
         got = G.run_gpu(db, spec, max_workgroups=max_wg, rows_per_item=rows_per_item)
         G.assert_same(got, oracle.run(spec, tables), name)
+
+
+# the damaged column's part in the query: (filters, group keys, sums), none of
+# them an atom on the column
+CORRUPT = {
+    "delta key": ("day", ["day"], ["a"]),
+    "delta value": ("day", ["k6"], ["day"]),
+    "wide delta value": ("ramp", ["k6"], ["ramp"]),
+    "for value": ("w25", ["k6"], ["w25"]),
+    "wide for value": ("w26", ["k6"], ["w26"]),
+    "dict value": ("dic", ["k6"], ["dic"]),
+    "dict key": ("dkey", ["dkey"], ["b"]),
+}
+
+
+@pytest.mark.parametrize("keep", ["every row", "few rows"])
+@pytest.mark.parametrize("what", sorted(CORRUPT))
+def test_corrupt_value_header_reported(ctx, what, keep):
+    """A damaged header of a column that no atom reads: mini blocks taken in
+    place (every row kept) and rows gathered one by one."""
+    from paper_2605_10511_amd import dpf
+    col, keys, sums = CORRUPT[what]
+    t = _table(20_000, 5)
+    filters = [] if keep == "every row" else [_lt(40)]
+    assert (t["a"][4 * 256:6 * 256] < 40).any()
+    spec = _spec(filters, keys, [{"op": "COUNT"}] + [{"op": "SUM", "terms": [_s(c)]} for c in sums])
+    want = oracle.run(spec, {"t": t})
+    db = G.make_db(ctx, {"t": t}, {"t": ENC}, placement="HOST_MAPPED")
+    offs = db.tables["t"][col].debug_offsets()
+    saved = int(offs[5])
+    G.say(f"corrupt {what}, {keep}")
+    offs[5] = saved + 3  # no longer a whole number of 8-word groups
+    with pytest.raises(dpf.DpfError) as e:
+        G.run_gpu(db, spec)
+    assert e.value.code == dpf.DPF_ERR_CORRUPT
+    offs[5] = saved
+    G.assert_same(G.run_gpu(db, spec), want, "after repair")
