@@ -1667,13 +1667,21 @@ dpf_status check_fused_opts(int32_t n, const dpf_exec_opts& o) {
     return DPF_OK;
 }
 
-// One launch of the persistent fused kernel over n plans.
-// One launch of the general or the lean kernel over the n plans idx names.
-dpf_status launch_fused_part(dpf_ctx ctx, int32_t n, const int32_t* idx, const dpf_plan* all, const dpf_exec_opts& o,
-                             const FusedWorkspace& ws, hipStream_t s) {
+// One launch of the general or the lean kernel.
+struct FusedLaunch {
+    BatchArgs a;
+    bool lean;
+    int waves, grid;
+    size_t lds;
+};
+
+// The launch over the n plans idx names, with every check that can refuse it;
+// enqueues nothing.
+dpf_status prepare_fused(dpf_ctx ctx, int32_t n, const int32_t* idx, const dpf_plan* all, const dpf_exec_opts& o,
+                         const FusedWorkspace& ws, FusedLaunch& L) {
     dpf_plan plans[kMaxBatch];
     for (int i = 0; i < n; ++i) plans[i] = all[idx[i]];
-    BatchArgs a;
+    BatchArgs& a = L.a;
     std::memset(&a, 0, sizeof a);
     a.nq = n;
     a.counters = ws.counters;
@@ -1829,9 +1837,10 @@ dpf_status launch_fused_part(dpf_ctx ctx, int32_t n, const int32_t* idx, const d
     a.item_start[n] = (int32_t)items;
     // no more workgroups than items: an idle workgroup still claims and signs off
     grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, items));
-    if (lean) HIP_TRY(launch_lean(a, waves, grid, lds, s));
-    else HIP_TRY(launch_fused(a, waves, grid, lds - kLdsStrTabBytes, s));  // the string table is static LDS
-    ctx->launches++;
+    L.lean = lean;
+    L.waves = waves;
+    L.grid = grid;
+    L.lds = lds;
     return DPF_OK;
 }
 
@@ -1863,23 +1872,47 @@ dpf_status launch_fused_batch(dpf_ctx ctx, int32_t n, const dpf_plan* plans, con
         nlean++;
     }
     const bool split = nlean > 0 && nlean < n && lean_rows >= kSplitRows;
-    if (ws.clear_bytes) {
-        HIP_TRY(launch_fill_i32((int32_t*)ws.clear, 0, (int64_t)(ws.clear_bytes / 4), s));
-        ctx->launches++;
-    }
-    for (int part = split ? 0 : 1; part < 2; ++part) {
+    const int parts = split ? 2 : 1;
+    // Every launch is settled before the first is enqueued: a refused batch
+    // has run nothing.
+    FusedLaunch L[2];
+    for (int part = 0; part < parts; ++part) {
         int k = 0;
         for (int i = 0; i < n; ++i)
             if (!split || (plans[i]->hq.lean.ok != 0) == (part == 0)) idx[k++] = i;
-        const dpf_status st = launch_fused_part(ctx, k, idx, plans, o, ws, s);
+        const dpf_status st = prepare_fused(ctx, k, idx, plans, o, ws, L[part]);
         if (st != DPF_OK) return st;
     }
-    for (int i = 0; i < n; ++i) {
-        if (plans[i]->hq.emit_copy) continue;
-        HIP_TRY(launch_emit(plans[i]->dq, plans[i]->hq, ws.agg[i], ws.status[i], s));
-        ctx->launches++;
+    hipError_t e = hipSuccess;
+    if (ws.clear_bytes) {
+        e = launch_fill_i32((int32_t*)ws.clear, 0, (int64_t)(ws.clear_bytes / 4), s);
+        if (e == hipSuccess) ctx->launches++;
     }
-    return DPF_OK;
+    for (int part = 0; part < parts && e == hipSuccess; ++part) {
+        const FusedLaunch& F = L[part];
+        e = F.lean ? launch_lean(F.a, F.waves, F.grid, F.lds, s)
+                   : launch_fused(F.a, F.waves, F.grid, F.lds - kLdsStrTabBytes, s);  // the string table is static LDS
+        if (e == hipSuccess) ctx->launches++;
+    }
+    for (int i = 0; i < n && e == hipSuccess; ++i) {
+        if (plans[i]->hq.emit_copy) continue;
+        e = launch_emit(plans[i]->dq, plans[i]->hq, ws.agg[i], ws.status[i], s);
+        if (e == hipSuccess) ctx->launches++;
+    }
+    if (e == hipSuccess) return DPF_OK;
+    // Some launch failed after others were enqueued (a captured one is the
+    // caller's to discard): no rows may stay in the group tables, which later
+    // executions expect empty, and nothing may still run on the plans, to
+    // which no result will hold a reference.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+        for (int i = 0; i < n; ++i) {
+            (void)launch_fill_i32((int32_t*)ws.agg[i], 0, (int64_t)(agg_table_bytes(plans[i]->hq) / 4), s);
+            (void)launch_fill_i32((int32_t*)ws.status[i], 0, 64, s);
+        }
+        (void)hipStreamSynchronize(s);
+    }
+    return hip_fail(e, "fused launch");
 }
 
 // The result handle of an execution; with_event records a completion event

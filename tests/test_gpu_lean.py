@@ -214,3 +214,37 @@ def test_corrupt_value_header_reported(ctx, what, keep):
     assert e.value.code == dpf.DPF_ERR_CORRUPT
     offs[5] = saved
     G.assert_same(G.run_gpu(db, spec), want, "after repair")
+
+
+def test_refused_split_batch_leaves_no_trace(ctx):
+    """A batch for both kernels whose join plan does not fit the workgroup's LDS
+    is refused before anything runs: the scan's group table (above 8,192
+    entries, written to the host by a launch of its own) stays empty."""
+    import torch
+    from paper_2605_10511_amd import dpf
+    n = 1 << 21
+    t = {c: v for c, v in _table(n, 6).items() if c in ("a", "b", "k9k", "h20")}
+    big = {"k": np.arange(8192, dtype=np.int32), "p": (np.arange(8192) % 5).astype(np.int32)}     # 128 KB in LDS
+    small = {"k": np.arange(1024, dtype=np.int32), "p": (np.arange(1024) % 3).astype(np.int32)}   # 16 KB
+    tables = {"t": t, "big": big, "small": small}
+    join = {"fact": "t", "filters": [_lt(500)],
+            "probes": [{"fk": "k9k", "dim": "big", "key": "k", "filters": [], "payloads": ["p"]},
+                       {"fk": "a", "dim": "small", "key": "k", "filters": [], "payloads": ["p"]}],
+            "group_by": [{"probe": 0, "payload": 0}, {"probe": 1, "payload": 0}],
+            "aggs": [{"op": "COUNT"}, {"op": "SUM", "terms": [_s("b")]}]}
+    specs = [_spec([_lt(700)], ["k9k"], [{"op": "COUNT"}, {"op": "SUM", "terms": [_s("b")]}]), join]
+    db = G.make_db(ctx, tables)
+    want = [oracle.run(s, tables) for s in specs]
+    plans = [db.plan(s) for s in specs]
+    for run in (dpf.execute, dpf.execute_noalloc):
+        G.say("refused split batch", run.__name__)
+        before = ctx.info().launches
+        with pytest.raises(dpf.DpfError) as e:
+            run(ctx, plans, lds_hash_bytes=150 * 1024)
+        assert e.value.code == dpf.DPF_ERR_UNSUPPORTED
+        assert ctx.info().launches == before
+        res = run(ctx, plans)
+        torch.cuda.synchronize()
+        for i in range(2):
+            G.assert_same(res.get(i), want[i], f"{run.__name__} {i}")
+        res.release()
