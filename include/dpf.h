@@ -369,7 +369,7 @@ typedef struct {
 /* Enqueues n >= 1 plans on stream.  FUSED runs them all in ONE launch of the
  * persistent kernel, which claims (plan, row range) work items from a device
  * queue (two launches where some plans have probes or string atoms and the
- * others scan 2M rows or more; a plan whose group table is hashed or exceeds
+ * others take tens of millions of rows; a plan whose group table is hashed or exceeds
  * 8,192 accumulators has its records written by a small launch more);
  * FRAGMENTED runs each plan as a sequence of separate kernels with materialised
  * intermediates (it allocates on first use and is not meant for graph capture).

@@ -175,6 +175,7 @@ struct dpf_plan_s {
     int32_t lds_budget = -2;
     int32_t naggs_out = 0;
     int32_t nacc_listed = 1;  // the row count and every SUM and AVG, equal ones included
+    double lean_saving = 0;   // a plan for the lean kernel: what that saves, in scanned rows (kSplitRows)
     bool issued = false;
     // The descriptor, block list and zeroed workspace go to the device on the
     // context's upload stream from this pinned staging copy; executions wait
@@ -926,11 +927,18 @@ constexpr int64_t kMbPerLoneItem = 128;  // a lone plan without string atoms
 constexpr int kTargetWavesPerCU = 24;       // string stage: 6 waves per SIMD (its register occupancy)
 constexpr int kTargetWavesPerCUNoStr = 24;  // without it: also 6 waves per SIMD
 constexpr int kLeanWavesPerCU = 16;         // lean kernel: 4 waves per SIMD (its registers)
-// Rows that a mixed batch's plans for the lean kernel must scan to be launched
-// by themselves: over 2M rows the lean kernel gains 4 to 45 us, more than a
-// launch costs (6 us), over 1M rows of a selective scan nothing.  (64 queries, half of them
-// with probes: 923 us in one launch, 646 in two.)
-constexpr int64_t kSplitRows = 2 << 20;
+// The plans of a mixed batch that the lean kernel can take get a launch of
+// their own once it saves what the second launch costs: 25 to 35 us, since one
+// follows the other and each has its own start, queue and end.  The saving is
+// counted in scanned rows, 1 us a million, with kSplitKept more for a row that
+// the atoms keep (estimated from the columns' ranges) and kSplitRun where the
+// rows are in order of a group key in device memory (the general kernel adds
+// such rows one by one at one address).  One launch and two, us, beside a join
+// over 250,000 rows: 2.2M rows, one in eight kept, 69 and 77; 8M 82 and 91; 32M
+// 166 and 146; 64M 290 and 215; 2M rows without atoms 77 and 82; 4.4M 105 and
+// 92; 2.2M by sorted day 733 and 104.
+constexpr int64_t kSplitRows = 40 << 20;
+constexpr double kSplitKept = 8, kSplitRun = 64;
 
 // Places the plan's dimension tables and group table in the workgroup's LDS
 // shared area within budget; fills lds offsets and lds_shared.
@@ -1145,6 +1153,32 @@ void fill_lean(const dpf_plan_desc* desc, DevQuery& q, const std::vector<int64_t
     const int64_t one = (q.ngroups + 1) * q.nacc * 8;
     while (L.log2r < kMaxLeanLog2r && (one << (L.log2r + 1)) <= kLeanAggBytes) ++L.log2r;
     L.ok = 1;
+}
+}  // namespace
+
+namespace {
+// The plan's saving in the lean kernel as kSplitRows counts it.  The share of
+// rows that an atom keeps is that of its values in the column's range.
+double lean_saving(const dpf_plan_desc* desc, const DevQuery& q) {
+    if (!q.lean.ok) return 0;
+    double kept = (double)q.nrows;
+    for (int p = 0; p < q.npreds; ++p) {
+        const DevPred& P = q.preds[p];
+        const HostColumn& c = desc->cols[P.col]->host;
+        const bool dict = c.enc == DPF_ENC_DICT;
+        const double lo = dict ? 0 : (double)c.minv, hi = dict ? (double)c.dict.size() - 1 : (double)c.maxv;
+        double n = hi - lo + 1;  // PK_NE
+        if (P.kind == PK_RANGE) n = std::min((double)P.hi, hi) - std::max((double)P.lo, lo) + 1;
+        else if (P.kind == PK_INMASK) n = __builtin_popcountll(P.mask);
+        else if (P.kind == PK_INLIST) n = P.n_in;
+        else if (P.kind == PK_FALSE) n = 0;
+        kept *= std::min(1.0, std::max(0.0, n / std::max(1.0, hi - lo + 1)));
+    }
+    bool run = false;
+    for (int k = 0; k < q.nkeys; ++k) run |= q.cols[q.loads[q.keys[k].slot].col].enc == ENC_DELTA;
+    run = run && !q.agg_hash && !q.agg_lds;
+    const double scanned = q.prune_mb ? (double)q.nlive * q.prune_mb * kMB : (double)q.nrows;
+    return scanned + (run ? kSplitRun : kSplitKept) * std::min(kept, scanned);
 }
 }  // namespace
 
@@ -1482,6 +1516,7 @@ extern "C" dpf_status dpf_plan_build(dpf_ctx ctx, const dpf_plan_desc* desc, dpf
     q.nlive = (int32_t)live.size();
     q.prune_mb = prune_mb;
     q.fs_dfa = fs_dfa.empty() ? nullptr : d + dfa_off;
+    p->lean_saving = lean_saving(desc, q);
     // Asynchronous upload on the context's upload stream: a fill kernel
     // zeroes the group table, status and queue counters, and the descriptor
     // and block list are copied from pinned staging.  The first executions
@@ -1860,18 +1895,16 @@ dpf_status launch_fused_batch(dpf_ctx ctx, int32_t n, const dpf_plan* plans, con
         }
     }
     // The lean kernel takes a batch whose plans all qualify.  Of a mixed one it
-    // takes the plans that do, in a launch of their own, once they scan
-    // kSplitRows rows.
+    // takes the plans that do, in a launch of their own, where that pays
+    // (kSplitRows).
     int32_t idx[kMaxBatch];
-    int64_t lean_rows = 0;
+    double saving = 0;
     int nlean = 0;
     for (int i = 0; i < n; ++i) {
-        const DevQuery& q = plans[i]->hq;
-        if (!q.lean.ok) continue;
-        lean_rows += q.live ? (int64_t)q.nlive * q.prune_mb * kMB : q.nrows;
-        nlean++;
+        saving += plans[i]->lean_saving;
+        nlean += plans[i]->hq.lean.ok != 0;
     }
-    const bool split = nlean > 0 && nlean < n && lean_rows >= kSplitRows;
+    const bool split = nlean > 0 && nlean < n && saving >= (double)kSplitRows;
     const int parts = split ? 2 : 1;
     // Every launch is settled before the first is enqueued: a refused batch
     // has run nothing.

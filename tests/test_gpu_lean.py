@@ -248,3 +248,37 @@ def test_refused_split_batch_leaves_no_trace(ctx):
         for i in range(2):
             G.assert_same(res.get(i), want[i], f"{run.__name__} {i}")
         res.release()
+
+
+# scans beside a join plan: the batch is split once they save enough, 20 of
+# them that keep one row in eight, 5 that keep all, one in order of a key whose
+# table is in device memory; never for a sum of 64-bit values
+@pytest.mark.parametrize("filt, group, col, plans, split", [
+    ([_lt(125)], "k6", "b", 20, True), ([_lt(125)], "k6", "b", 19, False), ([], "k6", "b", 5, True),
+    ([], "k6", "b", 4, False), ([], "day", "b", 1, True), ([_lt(125)], "k6", "wide", 20, False),
+    ([_lt(125), {"col": "dkey", "op": "IN", "values": [11, 12, 400, 90000]}], "dkey", "dic", 20, True)])
+def test_split_launches(ctx, filt, group, col, plans, split):
+    import torch
+    from paper_2605_10511_amd import dpf
+    t = _table(1 << 20, 7)
+    dim = {"k": np.arange(0, 9000, 2, dtype=np.int32), "p": (np.arange(0, 9000, 2) % 5).astype(np.int32)}
+    tables = {"t": t, "d": dim}
+    join = {**_spec([], [], [{"op": "COUNT"}]), "group_by": [{"probe": 0, "payload": 0}, {"probe": 1, "payload": 0}],
+            "probes": [{"fk": fk, "dim": "d", "key": "k", "filters": [], "payloads": ["p"]} for fk in ("k9k", "a")]}
+    specs = [_spec(filt, [group], [{"op": "COUNT"}, {"op": "SUM", "terms": [_s(col)]}]), join]
+    want = [oracle.run(s, tables) for s in specs]
+    db = G.make_db(ctx, tables, {"t": ENC})
+    batch = [db.plan(specs[0]) for _ in range(plans)] + [db.plan(join)]
+    for run in (dpf.execute, dpf.execute_noalloc):
+        G.say("split launches", filt, group, col, plans, run.__name__)
+        before = ctx.info().launches
+        with pytest.raises(dpf.DpfError) as e:  # a table of 128 KB and the waves' own LDS do not fit
+            run(ctx, batch, lds_hash_bytes=160 * 1024, waves_per_wg=16)
+        assert e.value.code == dpf.DPF_ERR_UNSUPPORTED
+        assert ctx.info().launches == before
+        res = run(ctx, batch)
+        assert ctx.info().launches == before + (2 if split else 1) + (run is dpf.execute_noalloc)
+        torch.cuda.synchronize()
+        for i in range(len(batch)):
+            G.assert_same(res.get(i), want[i == plans], f"{run.__name__} {i}")
+        res.release()
