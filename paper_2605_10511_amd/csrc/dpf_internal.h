@@ -317,6 +317,7 @@ struct BatchArgs {
     int32_t guided_mb;
     int32_t big_share;
     int32_t small_mb;
+    int32_t walk;         // claims look at the other item ranges one by one
 };
 
 // Guided work items of XCD x: its mini blocks start at r0 and make the

@@ -395,9 +395,13 @@ __device__ __forceinline__ uint32_t* ctr(const BatchArgs& a, int i) { return a.c
 // place among those homed on its XCD; those after the last workgroup's are
 // claimed.  (Claims on one head are served one at a time, about 0.1 us each: 5M
 // comments, an item a workgroup, took 93 us with first items claimed too, 87
-// without.)  The other ranges' heads are read together: one after the
-// other they kept every workgroup for seven waits at the launch's end (40,000
-// rows: 40.3 us, now 37.3).
+// without.)  Then the other ranges.  A lone plan with a few items a workgroup
+// reads the heads of all that are left together: one after the other they kept
+// every workgroup for seven waits at the launch's end (40,000 rows: 40.3 us,
+// now 37.3).  With many items (a.walk) ranges end at different times, and a
+// workgroup looks for the next one often: there one head a look, or the reads
+// hold up the claims (two scans of 2.2M rows and four joins over 1M in one
+// batch: 113 us together, 99 so).
 template <class N>
 __device__ __forceinline__ int claim(const BatchArgs& a, int home, uint32_t& drained, bool first, int lane, N n, int& x) {
     auto given = [&](int y) { return (int)gridDim.x > y ? (int)((gridDim.x - 1u - (uint32_t)y) / kXcds + 1u) : 0; };
@@ -412,12 +416,15 @@ __device__ __forceinline__ int claim(const BatchArgs& a, int home, uint32_t& dra
             if (j < left(x)) return (int)j + given(x);
         }
         drained |= 1u << x;
-        const int y = lane & (kXcds - 1);
-        const uint32_t h = __hip_atomic_load(ctr(a, y), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t open = (uint32_t)__ballot(lane < kXcds && h < left(y)) & ~drained;
-        if (open == 0) return -1;
-        const uint32_t from = (open >> home) | (open << (kXcds - home));  // the next after home
-        x = (home + __builtin_ctz(from)) & (kXcds - 1);
+        const uint32_t rest = ~drained & ((1u << kXcds) - 1u);
+        if (rest == 0) return -1;
+        const uint32_t from = (rest >> home) | (rest << (kXcds - home));
+        x = (home + __builtin_ctz(from)) & (kXcds - 1);  // the next after home
+        const uint32_t look = a.walk ? 1u << x : rest;
+        uint32_t h = ~0u;
+        if (lane < kXcds && ((look >> lane) & 1u))
+            h = __hip_atomic_load(ctr(a, lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        drained |= look & ~(uint32_t)__ballot(h < left(lane & (kXcds - 1)));  // (x itself: the next turn passes it by)
     }
 }
 
@@ -521,7 +528,7 @@ __device__ __forceinline__ void finish_launch(const BatchArgs& a, int32_t* ctrl,
 // kStr: 0 no string atom in the batch, 1 string atoms on VARLEN columns, 2
 // also an FSST atom.  kHash: some plan aggregates into a hash group table.
 template <int kStr, bool kHash>
-__global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(kStr == 2 ? 5 : kStr ? 6 : 4, 8))) void fused_kernel(BatchArgs a) {
+__global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(kStr == 2 ? 5 : 6, 8))) void fused_kernel(BatchArgs a) {
     extern __shared__ __align__(16) uint8_t smem[];
     // Static LDS: its address is known when the kernel is compiled, so the
     // string scan's table reads take it as an immediate offset.
@@ -539,7 +546,7 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(kStr
     const int total_items = a.item_start[a.nq];
 
     const int home = (int)(blockIdx.x % kXcds);
-    uint32_t drained = 0;  // thread 0: item ranges found empty
+    uint32_t drained = 0;  // wave 0: item ranges found empty
     unsigned long long sink = 0;  // old values of this thread's device-scope atomics
     bool direct = false;          // some plan aggregated straight into global memory
     int cur = -1;

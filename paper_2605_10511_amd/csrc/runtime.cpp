@@ -1870,6 +1870,7 @@ dpf_status prepare_fused(dpf_ctx ctx, int32_t n, const int32_t* idx, const dpf_p
     }
     if (items > INT32_MAX) return fail(DPF_ERR_UNSUPPORTED, "too many work items; raise rows_per_item");
     a.item_start[n] = (int32_t)items;
+    a.walk = !a.guided_mb && (n > 1 || items > 2 * grid);
     // no more workgroups than items: an idle workgroup still claims and signs off
     grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, items));
     L.lean = lean;
