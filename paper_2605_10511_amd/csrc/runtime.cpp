@@ -924,8 +924,12 @@ constexpr int64_t kAggLdsMax = 16 * 1024;
 
 constexpr int64_t kMbPerItem = 64;       // 16,384 rows
 constexpr int64_t kMbPerLoneItem = 128;  // a lone plan without string atoms
-constexpr int kTargetWavesPerCU = 24;       // string stage: 6 waves per SIMD (its register occupancy)
-constexpr int kTargetWavesPerCUNoStr = 24;  // without it: also 6 waves per SIMD
+// Waves per CU, as the registers of each kernel allow: 6 per SIMD, with the FSST
+// walk 5.  (FSST with 6: every sixth workgroup starts when another has ended.
+// 8M comments of which two in three match, an item a workgroup: 178 us, with 5
+// 135; where few match the same, 112.)
+constexpr int kTargetWavesPerCU = 24;
+constexpr int kTargetWavesPerCUFsst = 20;
 constexpr int kLeanWavesPerCU = 16;         // lean kernel: 4 waves per SIMD (its registers)
 // The plans of a mixed batch that the lean kernel can take get a launch of
 // their own once it saves what the second launch costs: 25 to 35 us, since one
@@ -1793,7 +1797,7 @@ dpf_status prepare_fused(dpf_ctx ctx, int32_t n, const int32_t* idx, const dpf_p
     // copy a workgroup), in the smallest workgroups.  With string atoms 4, where
     // those fit: larger ones wait longer at an item's end (6M FSST comments 154
     // us with 4, 190 with 8).
-    const int target = lean ? kLeanWavesPerCU : str ? kTargetWavesPerCU : kTargetWavesPerCUNoStr;
+    const int target = lean ? kLeanWavesPerCU : fsst ? kTargetWavesPerCUFsst : kTargetWavesPerCU;
     if (waves == 0) {
         waves = 4;
         int best = 0;
