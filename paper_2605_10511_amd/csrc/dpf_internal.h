@@ -312,24 +312,16 @@ struct BatchArgs {
     int32_t lean_group;   // mini blocks staged together: 4, 2 or 1
     int32_t lean_log2r;   // copies of an LDS group table: at most 2^lean_log2r
     // A lone plan's guided items (else guided_mb 0): its mini blocks (of its
-    // surviving blocks), the large items' share of them in eighths, the small
-    // items' mini blocks (the large: mb_per_item).
+    // surviving blocks); those of an XCD, from x * xcd_mb on (the last XCDs' may
+    // be fewer or none); an XCD's items, the first xcd_big of mb_per_item mini
+    // blocks, the rest of small_mb.
     int32_t guided_mb;
-    int32_t big_share;
+    int32_t xcd_mb;
+    int32_t xcd_items;
+    int32_t xcd_big;
     int32_t small_mb;
     int32_t walk;         // claims look at the other item ranges one by one
 };
-
-// Guided work items of XCD x: its mini blocks start at r0 and make the
-// returned number of items, the first nbig of mb_per_item, the rest of
-// small_mb mini blocks.
-__host__ __device__ inline int guided_start(int mb, int x) { return (int)((int64_t)mb * x / kXcds); }
-__host__ __device__ inline int guided_items(const BatchArgs& a, int x, int& r0, int& nbig) {
-    r0 = guided_start(a.guided_mb, x);
-    const int len = guided_start(a.guided_mb, x + 1) - r0;
-    nbig = (int)((uint32_t)(len / 8 * a.big_share) / (uint32_t)a.mb_per_item);
-    return nbig + (int)((uint32_t)(len - nbig * a.mb_per_item + a.small_mb - 1) / (uint32_t)a.small_mb);
-}
 
 // Hash build over a dimension table (optionally joined: the rows must find
 // their foreign keys in the tables of sub[], probed from device memory).

@@ -437,16 +437,17 @@ __device__ __forceinline__ int claim_item(const BatchArgs& a, int home, uint32_t
 
 // Claims of a lone plan: each XCD's eighth of its mini blocks (a pruned plan's:
 // of its surviving blocks') is cut into large items and, at its end, small ones
-// (guided_items), so that all workgroups end together (24M-row summary: 185 us
-// with one size, 179 so).  False: none left.
+// so that all workgroups end together (24M-row summary: 185 us with one size,
+// 179 so).  Every XCD has the same items; the last ones' may be empty.  False:
+// none left.
 __device__ __forceinline__ bool claim_guided(const BatchArgs& a, int home, uint32_t& drained, bool first, int lane, int& mb0,
                                              int& mb1) {
-    int x, r0, nbig;
-    const int j = claim(a, home, drained, first, lane, [&](int y) { return (uint32_t)guided_items(a, y, r0, nbig); }, x);
+    int x;
+    const int j = claim(a, home, drained, first, lane, [&](int) { return (uint32_t)a.xcd_items; }, x);
     if (j < 0) return false;
-    guided_items(a, x, r0, nbig);
-    mb0 = r0 + (j < nbig ? j * a.mb_per_item : nbig * a.mb_per_item + (j - nbig) * a.small_mb);
-    mb1 = min(mb0 + (j < nbig ? a.mb_per_item : a.small_mb), guided_start(a.guided_mb, x + 1));
+    const bool big = j < a.xcd_big;
+    mb0 = x * a.xcd_mb + (big ? j * a.mb_per_item : a.xcd_big * a.mb_per_item + (j - a.xcd_big) * a.small_mb);
+    mb1 = min(mb0 + (big ? a.mb_per_item : a.small_mb), min((x + 1) * a.xcd_mb, a.guided_mb));
     return true;
 }
 

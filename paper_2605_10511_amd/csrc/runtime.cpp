@@ -1822,8 +1822,8 @@ dpf_status prepare_fused(dpf_ctx ctx, int32_t n, const int32_t* idx, const dpf_p
     // for the lean kernel and batches about three items a workgroup, for a
     // lone plan of the general kernel one, or the fewest equal ones up to
     // kMbPerLoneItem.  (At an item's end its waves wait for the slowest, then for the
-    // claim.  Three items and one: 5M comments 113 and 87 us, 6M FSST comments
-    // 157 and 113, 16M comments 183 and 154; 48M-row star join with items of 64
+    // claim.  Three items and one: 5M comments 120 and 93 us, 6M FSST comments
+    // 169 and 115, 16M comments 184 and 154; 48M-row star join with items of 64
     // and 128 mini blocks 184 and 175, of 256 206.)  Mini blocks of strings differ
     // in what they take: a share above kMbPerItem goes in items of that size
     // (60M rows in items of 128 and 64: VARLEN 537 and 408 us, FSST 702 and 633).
@@ -1843,11 +1843,27 @@ dpf_status prepare_fused(dpf_ctx ctx, int32_t n, const int32_t* idx, const dpf_p
             const int64_t k = std::max<int64_t>((share + most - 1) / most, 1);
             mb_per_item = whole((share + k - 1) / k);
         }
+        // Guided: a lean plan's items, and strings' of kMbPerItem, for seven
+        // eighths of the mini blocks, then smaller ones.  Strings in one item a
+        // workgroup: where rounding up to whole runs would leave workgroups
+        // without an item (one in twenty and more), every workgroup gets its share
+        // rounded down, and the rest goes in items of a mini block a wave, claimed.
+        // (Rounded up / so: 8M comments of which two in three match 337 and 295
+        // us, one in ten 171 and 154; 16M, few match, 372 and 347.  Even shares
+        // without claims: 317, 167, 364.)
         if (guided) {
-            const bool one = !lean && share <= kMbPerItem;  // a workgroup's one item
+            const bool one = !lean && share <= kMbPerItem;
+            const int64_t xcd_mb = (scan_mb + kXcds - 1) / kXcds, down = scan_mb / grid / waves * waves;
+            int64_t big = one ? xcd_mb / mb_per_item : xcd_mb / 8 * 7 / mb_per_item;
+            if (one && grid >= kXcds && down >= 2 * waves && 20 * scan_mb < 19 * grid * mb_per_item) {
+                mb_per_item = down;
+                big = grid / kXcds;
+            }
             a.guided_mb = (int32_t)scan_mb;
-            a.big_share = one ? 8 : 7;
+            a.xcd_mb = (int32_t)xcd_mb;
+            a.xcd_big = (int32_t)big;
             a.small_mb = (int32_t)(one ? waves : whole(mb_per_item / (lean ? 2 : 4)));
+            a.xcd_items = a.xcd_big + (int32_t)((xcd_mb - big * mb_per_item + a.small_mb - 1) / a.small_mb);
         }
         // a pruned plan's items are slices of its blocks: even slices
         for (int i = 0; i < n && !guided; ++i)
@@ -1865,13 +1881,7 @@ dpf_status prepare_fused(dpf_ctx ctx, int32_t n, const int32_t* idx, const dpf_p
         items += q.live ? (int64_t)q.nlive * ((q.prune_mb + mb_per_item - 1) / mb_per_item)
                         : (q.nmb + mb_per_item - 1) / mb_per_item;
     }
-    if (a.guided_mb) {
-        items = 0;
-        for (int x = 0; x < kXcds; ++x) {
-            int r0, nbig;
-            items += guided_items(a, x, r0, nbig);
-        }
-    }
+    if (a.guided_mb) items = (int64_t)kXcds * a.xcd_items;
     if (items > INT32_MAX) return fail(DPF_ERR_UNSUPPORTED, "too many work items; raise rows_per_item");
     a.item_start[n] = (int32_t)items;
     a.walk = !a.guided_mb && (n > 1 || items > 2 * grid);

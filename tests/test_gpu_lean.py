@@ -282,3 +282,26 @@ def test_split_launches(ctx, filt, group, col, plans, split):
         for i in range(len(batch)):
             G.assert_same(res.get(i), want[i == plans], f"{run.__name__} {i}")
         res.release()
+
+
+# lone string plans whose share of 8 mini blocks and more a workgroup does not
+# divide: rounded down, the rest claimed; an XCD's range that ends early or is
+# empty; one mini block
+@pytest.mark.parametrize("rows, max_wg", [(157 * 256 - 77, 16), (157 * 256, 11), (129 * 256 + 1, 8), (200 * 256, 8), (9 * 256, 0), (1, 0)])
+def test_string_items_taken_once(ctx, rows, max_wg):
+    from tests.conftest import to_strings
+    t = _table(rows, 9)
+    rng = np.random.default_rng(9)
+    words = [b"alpha", b"beta", b"gamma", b"delta", b"alphabeta"]
+    t["s"] = to_strings([b" ".join(words[j] for j in rng.integers(0, 5, 4)) for _ in range(rows)])
+    db = G.make_db(ctx, {"t": t}, {"t": ENC}, chunk_rows=2048)
+    like = {"col": "s", "op": "STR_CONTAINS_SEQ", "s1": b"alpha", "s2": b"gamma"}
+    for filters in ([like], [{"col": "day", "op": "GE", "value": 3}, like], [{"col": "day", "op": "LE", "value": 51}]):
+        spec = _spec(filters, ["k6"], SUMS["plain"])
+        G.say("string items", rows, max_wg, len(filters))
+        got = G.run_gpu(db, spec, max_workgroups=max_wg)
+        want = oracle.run(spec, {"t": t})
+        if len(want) == 0:
+            assert len(got) == 0
+        else:
+            G.assert_same(got, want, f"{rows} {max_wg} {filters}")
