@@ -150,6 +150,7 @@ enum : uint32_t { ST_CORRUPT = 1u, ST_CAPACITY = 2u, ST_UNSUPPORTED = 4u, ST_DUP
 // 32-bit offsets u = value - ref.
 constexpr int kLeanTiles = 16;    // mini blocks whose headers a wave prepares at a time
 constexpr int kLeanEnts = kMaxPreds + kMaxSlots;
+constexpr int kLeanWidth = 32;    // widest packed value: what a shift of up to 31 leaves of a dword pair
 // Copies of an LDS group table: at most 8, in 8 KB.  (6 groups: the 24M-row
 // summary took 204 us with 4 copies, 166 with 8, 164 with 16; the 60M-row filter
 // 216, 215 and 224, 266 with 32.)
@@ -166,7 +167,7 @@ struct LeanEnt {            // one column as an atom or a value slot reads it
     uint32_t nwords;
     int32_t enc;
     int32_t kind;           // atom: PK_*
-    int32_t maxw;           // widest mini block of the column, at most 25
+    int32_t maxw;           // widest mini block of the column, at most kLeanWidth
     // Staging area of the column's packed words, for one mini block: its place
     // in the wave's, whether this entry copies them (0: an entry before it with
     // the same column does; 2: for a later one too), its bytes.

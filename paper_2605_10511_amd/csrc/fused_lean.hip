@@ -181,17 +181,17 @@ __device__ __forceinline__ uint4 lean_rec(const LeanWave& W, int e, int t) {
     return uniform_rec(W.recs[e * kLeanTiles + t]);
 }
 
-// The lane's four rows' values of b <= 25 bits: the 64 rows between them are
-// 2 b whole dwords, so all four sit at bit (lane b) & 31 of a pair of dwords.
+// The lane's four rows' values of b <= kLeanWidth bits: the 64 rows between them
+// are 2 b whole dwords, so all four sit at bit (lane b) & 31 of a pair of dwords.
 __device__ __forceinline__ void lean_unpack(const uint8_t* stage, uint32_t b, int lane, uint32_t v[4]) {
     const uint32_t bp = (uint32_t)lane * b, sh = bp & 31u;
     const uint8_t* p = stage + ((bp >> 5) << 2);
+    const uint32_t keep = b ? ~0u >> (32u - b) : 0u;
     uint64_t w[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) w[k] = *reinterpret_cast<const u64_a4*>(p + (uint32_t)k * 8u * b);
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-        v[k] = __builtin_amdgcn_ubfe(__builtin_amdgcn_alignbit((uint32_t)(w[k] >> 32), (uint32_t)w[k], sh), 0u, b);  // b == 0: 0
+    for (int k = 0; k < 4; ++k) v[k] = __builtin_amdgcn_alignbit((uint32_t)(w[k] >> 32), (uint32_t)w[k], sh) & keep;
 }
 
 // ---------------------------------------------------------------------------
@@ -675,7 +675,7 @@ __device__ __forceinline__ void lean_gather(CQ& Q, const LeanWave& W, int c0, co
                 const uint32_t b = hdr_width(rec.y);
                 const uint32_t v = __builtin_amdgcn_alignbit((uint32_t)(w[s][r] >> 32), (uint32_t)w[s][r],
                                                              ((row[r] & 255u) * b) & 31u);
-                u[(s0 + s) * 4 + r] = __builtin_amdgcn_ubfe(v, 0u, b) + rec.z;
+                u[(s0 + s) * 4 + r] = (b < 32u ? __builtin_amdgcn_ubfe(v, 0u, b) : v) + rec.z;  // (it takes 5 bits of b)
             }
         }
     }

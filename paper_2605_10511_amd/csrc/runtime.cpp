@@ -1033,7 +1033,10 @@ namespace {
 // atoms only; no probes (the star query over 6M fact rows took 75 us there, 63
 // in the general kernel; over 48M 174 and 183); every value slot's range below
 // 2^32 (values are carried as 32-bit offsets from the range's start, exact
-// modulo 2^64 once widened); no slot twice as a key.
+// modulo 2^64 once widened); no column with mini blocks wider than 32 bits, each
+// of which would be decoded by the general kernel's code between the lean steps
+// (full-width 64-bit columns, one row in eight kept: 98 us, in the general kernel
+// 89); no slot twice as a key.
 void fill_lean(const dpf_plan_desc* desc, DevQuery& q, const std::vector<int64_t>& lo, const std::vector<int64_t>& hi) {
     LeanPlan& L = q.lean;
     L.ok = 0;
@@ -1041,6 +1044,11 @@ void fill_lean(const dpf_plan_desc* desc, DevQuery& q, const std::vector<int64_t
     auto narrow = [](int64_t a, int64_t b) { return b < a || (unsigned __int128)((__int128)b - a) < (uint64_t(1) << 32); };
     for (size_t s = 0; s < lo.size(); ++s)
         if (!narrow(lo[s], hi[s])) return;
+    auto wide = [&](int col) { return desc->cols[col]->host.max_width > kLeanWidth; };
+    for (int p = 0; p < q.npreds; ++p)
+        if (wide(q.preds[p].col)) return;
+    for (int l = 0; l < q.nloads; ++l)
+        if (wide(q.loads[l].col)) return;
     auto view = [&](int col, int64_t ref) {
         const DevCol& c = q.cols[col];
         LeanMore e{};
@@ -1076,13 +1084,12 @@ void fill_lean(const dpf_plan_desc* desc, DevQuery& q, const std::vector<int64_t
         L.more[n++] = e;
     }
     L.nents = n;
-    // Staging: 32 bytes a bit of width and mini block (those wider than 25
-    // bits are decoded another way), 16 more for the last row's dwords.  Of the
+    // Staging: 32 bytes a bit of width and mini block, 16 more for the last row's dwords.  Of the
     // atoms the first three are staged, of all entries the first 16; a column
     // that is both is staged once.
     for (int e = 0; e < n; ++e) {
         LeanEnt& E = L.ents[e];
-        E.maxw = std::min(desc->cols[L.more[e].col]->host.max_width, 25);
+        E.maxw = std::min(desc->cols[L.more[e].col]->host.max_width, kLeanWidth);
         E.stage_sz = (uint32_t)(32 * E.maxw);
         E.stage_off = E.stage_copy = 0;
         const bool atom = e < q.npreds;

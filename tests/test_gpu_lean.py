@@ -305,3 +305,31 @@ def test_string_items_taken_once(ctx, rows, max_wg):
             assert len(got) == 0
         else:
             G.assert_same(got, want, f"{rows} {max_wg} {filters}")
+
+
+# the widest packed values the 32-bit kernel takes (31 and 32 bits, full-width
+# 32-bit columns) and, with 33 bits and full-width 64-bit columns, those it does
+# not: atoms at both ends of the range, rows kept densely and sparsely
+@pytest.mark.parametrize("col", ["w31", "w32", "s32", "p32", "w33", "p64"])
+@pytest.mark.parametrize("rows", [257, 4096 + 1025])
+def test_widest_values(ctx, col, rows):
+    rng = np.random.default_rng(rows)
+    t = _table(rows, 10)
+    t["w31"] = rng.integers(-5, (1 << 31) - 5, rows, dtype=np.int64)
+    t["w32"] = rng.integers(1 << 40, (1 << 40) + (1 << 32), rows, dtype=np.int64)
+    t["s32"] = rng.integers(-(1 << 31), 1 << 31, rows, dtype=np.int64).astype(np.int32)
+    t["p32"] = rng.integers(-100, 100, rows, dtype=np.int32)
+    t["w33"] = rng.integers(0, 1 << 33, rows, dtype=np.int64)
+    t["p64"] = rng.integers(-100, 100, rows, dtype=np.int64)
+    lo, hi = {"w31": (-5, (1 << 31) - 6), "w32": (1 << 40, (1 << 40) + (1 << 32) - 1), "s32": (-(1 << 31), (1 << 31) - 1),
+              "p32": (-100, 99), "w33": (0, (1 << 33) - 1), "p64": (-100, 99)}[col]
+    t[col][:256:2], t[col][1:256:2] = lo, hi
+    db = G.make_db(ctx, {"t": t}, {"t": {**ENC, "p32": "PLAIN", "p64": "PLAIN"}}, chunk_rows=4096)
+    aggs = [{"op": "COUNT"}, {"op": "SUM", "terms": [_s(col)]}, {"op": "AVG", "terms": [_s("a")]}]
+    mid = (lo + hi) // 2
+    for f in ([], [_lt(30)], [{"col": col, "op": "GT", "value": lo}], [{"col": col, "op": "LT", "value": hi}],
+              [{"col": col, "op": "NE", "value": lo}], [{"col": col, "op": "NE", "value": hi}, _lt(40)],
+              [{"col": col, "op": "EQ", "value": hi}], [{"col": col, "op": "GE", "value": mid}, _lt(900)]):
+        spec = _spec(f, ["k6"], aggs)
+        G.say("widest values", col, rows, f)
+        G.assert_same(G.run_gpu(db, spec), oracle.run(spec, {"t": t}), f"{col} {rows} {f}")
