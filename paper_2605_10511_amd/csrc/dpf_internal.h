@@ -207,6 +207,7 @@ struct LeanPlan {
     int32_t log2r;          // copies of the LDS group table: up to 2^log2r
     int32_t stage_bytes;    // a wave's staging area for the packed words of one mini block
     int32_t dicts;          // value slots that hold a DICT column's values: bits
+    int32_t stage_first;    // a wave's first mini blocks have their value columns staged with the atoms'
     // Direct group tables: the key slots (bits), each with its largest value
     // and its stride.
     int32_t keys;

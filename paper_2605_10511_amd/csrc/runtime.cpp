@@ -1029,6 +1029,25 @@ void free_frag(dpf_plan p) {
 }  // namespace
 
 namespace {
+// The share of the rows that the plan's integer atoms keep, were the values of
+// each column spread evenly over its range.
+double kept_share(const dpf_plan_desc* desc, const DevQuery& q) {
+    double kept = 1;
+    for (int p = 0; p < q.npreds; ++p) {
+        const DevPred& P = q.preds[p];
+        const HostColumn& c = desc->cols[P.col]->host;
+        const bool dict = c.enc == DPF_ENC_DICT;
+        const double lo = dict ? 0 : (double)c.minv, hi = dict ? (double)c.dict.size() - 1 : (double)c.maxv;
+        double n = hi - lo + 1;  // PK_NE
+        if (P.kind == PK_RANGE) n = std::min((double)P.hi, hi) - std::max((double)P.lo, lo) + 1;
+        else if (P.kind == PK_INMASK) n = __builtin_popcountll(P.mask);
+        else if (P.kind == PK_INLIST) n = P.n_in;
+        else if (P.kind == PK_FALSE) n = 0;
+        kept *= std::min(1.0, std::max(0.0, n / std::max(1.0, hi - lo + 1)));
+    }
+    return kept;
+}
+
 // The plan in the lean kernel's form (LeanPlan), when it qualifies: integer
 // atoms only; no probes (the star query over 6M fact rows took 75 us there, 63
 // in the general kernel; over 48M 174 and 183); every value slot's range below
@@ -1163,28 +1182,22 @@ void fill_lean(const dpf_plan_desc* desc, DevQuery& q, const std::vector<int64_t
     L.log2r = 0;
     const int64_t one = (q.ngroups + 1) * q.nacc * 8;
     while (L.log2r < kMaxLeanLog2r && (one << (L.log2r + 1)) <= kLeanAggBytes) ++L.log2r;
+    // The value columns of a wave's first mini blocks come with the atoms'
+    // (40,000 rows: a fifth of a scan), but not over the host link for rows that
+    // the atoms are likely to drop (4M rows, one in 250 kept: 335 us with them,
+    // 221 without).
+    bool link = false;
+    for (int i = 0; i < desc->ncols; ++i) link |= desc->cols[i]->placement == DPF_PLACE_HOST_MAPPED;
+    L.stage_first = !link || kept_share(desc, q) * kMB >= 96;
     L.ok = 1;
 }
 }  // namespace
 
 namespace {
-// The plan's saving in the lean kernel as kSplitRows counts it.  The share of
-// rows that an atom keeps is that of its values in the column's range.
+// The plan's saving in the lean kernel as kSplitRows counts it.
 double lean_saving(const dpf_plan_desc* desc, const DevQuery& q) {
     if (!q.lean.ok) return 0;
-    double kept = (double)q.nrows;
-    for (int p = 0; p < q.npreds; ++p) {
-        const DevPred& P = q.preds[p];
-        const HostColumn& c = desc->cols[P.col]->host;
-        const bool dict = c.enc == DPF_ENC_DICT;
-        const double lo = dict ? 0 : (double)c.minv, hi = dict ? (double)c.dict.size() - 1 : (double)c.maxv;
-        double n = hi - lo + 1;  // PK_NE
-        if (P.kind == PK_RANGE) n = std::min((double)P.hi, hi) - std::max((double)P.lo, lo) + 1;
-        else if (P.kind == PK_INMASK) n = __builtin_popcountll(P.mask);
-        else if (P.kind == PK_INLIST) n = P.n_in;
-        else if (P.kind == PK_FALSE) n = 0;
-        kept *= std::min(1.0, std::max(0.0, n / std::max(1.0, hi - lo + 1)));
-    }
+    const double kept = kept_share(desc, q) * (double)q.nrows;
     bool run = false;
     for (int k = 0; k < q.nkeys; ++k) run |= q.cols[q.loads[q.keys[k].slot].col].enc == ENC_DELTA;
     run = run && !q.agg_hash && !q.agg_lds;
