@@ -175,6 +175,13 @@ struct dpf_plan_s {
     int32_t lds_budget = -2;
     int32_t naggs_out = 0;
     int32_t nacc_listed = 1;  // the row count and every SUM and AVG, equal ones included
+    // A plan for the lean kernel: the smallest work item asked for that it takes
+    // (it sets up headers for each; smaller ones go to the general kernel).  8M
+    // rows, general and lean kernel, us: one row in 8 kept, items of 256 rows 167
+    // and 265, 1,024 rows 104 and 117, 2,048 rows 92 and 85; one in 250 kept, 1,024
+    // rows 73 and 102, 2,048 rows 69 and 75, 3,072 rows 69 and 68; all kept, 256
+    // rows 338 and 250.
+    int32_t lean_min_rows = 0;
     double lean_saving = 0;   // a plan for the lean kernel: what that saves, in scanned rows (kSplitRows)
     bool issued = false;
     // The descriptor, block list and zeroed workspace go to the device on the
@@ -1194,13 +1201,19 @@ void fill_lean(const dpf_plan_desc* desc, DevQuery& q, const std::vector<int64_t
 }  // namespace
 
 namespace {
+// The rows of a lean plan come in order of a group key whose table is in device
+// memory: the general kernel adds such rows one by one at one address.
+bool lean_runs(const DevQuery& q) {
+    bool run = false;
+    for (int k = 0; k < q.nkeys; ++k) run |= q.cols[q.loads[q.keys[k].slot].col].enc == ENC_DELTA;
+    return run && !q.agg_hash && !q.agg_lds;
+}
+
 // The plan's saving in the lean kernel as kSplitRows counts it.
 double lean_saving(const dpf_plan_desc* desc, const DevQuery& q) {
     if (!q.lean.ok) return 0;
     const double kept = kept_share(desc, q) * (double)q.nrows;
-    bool run = false;
-    for (int k = 0; k < q.nkeys; ++k) run |= q.cols[q.loads[q.keys[k].slot].col].enc == ENC_DELTA;
-    run = run && !q.agg_hash && !q.agg_lds;
+    const bool run = lean_runs(q);
     const double scanned = q.prune_mb ? (double)q.nlive * q.prune_mb * kMB : (double)q.nrows;
     return scanned + (run ? kSplitRun : kSplitKept) * std::min(kept, scanned);
 }
@@ -1541,6 +1554,8 @@ extern "C" dpf_status dpf_plan_build(dpf_ctx ctx, const dpf_plan_desc* desc, dpf
     q.prune_mb = prune_mb;
     q.fs_dfa = fs_dfa.empty() ? nullptr : d + dfa_off;
     p->lean_saving = lean_saving(desc, q);
+    const double kept = kept_share(desc, q);
+    p->lean_min_rows = lean_runs(q) || kept >= 0.5 ? 0 : kept >= 0.05 ? 2048 : 3072;
     // Asynchronous upload on the context's upload stream: a fill kernel
     // zeroes the group table, status and queue counters, and the descriptor
     // and block list are copied from pinned staging.  The first executions
@@ -1726,6 +1741,11 @@ dpf_status check_fused_opts(int32_t n, const dpf_exec_opts& o) {
     return DPF_OK;
 }
 
+// The plan can run in the lean kernel, with these options.
+bool use_lean(dpf_plan p, const dpf_exec_opts& o) {
+    return p->hq.lean.ok && (o.rows_per_item == 0 || o.rows_per_item >= p->lean_min_rows);
+}
+
 // One launch of the general or the lean kernel.
 struct FusedLaunch {
     BatchArgs a;
@@ -1763,7 +1783,7 @@ dpf_status prepare_fused(dpf_ctx ctx, int32_t n, const int32_t* idx, const dpf_p
     a.str_stage = fsst ? 2 : str ? 1 : 0;
     a.pend_stage = pend;
     bool lean = true;
-    for (int i = 0; i < n; ++i) lean &= plans[i]->hq.lean.ok != 0;
+    for (int i = 0; i < n; ++i) lean &= use_lean(plans[i], o);
     auto lds_for = [&](int w) {
         if (lean)
             return kLdsCtrlBytes + (size_t)a.lds_shared + (size_t)a.lean_ents * sizeof(LeanEnt) +
@@ -1945,8 +1965,9 @@ dpf_status launch_fused_batch(dpf_ctx ctx, int32_t n, const dpf_plan* plans, con
     double saving = 0;
     int nlean = 0;
     for (int i = 0; i < n; ++i) {
+        if (!use_lean(plans[i], o)) continue;
         saving += plans[i]->lean_saving;
-        nlean += plans[i]->hq.lean.ok != 0;
+        nlean++;
     }
     const bool split = nlean > 0 && nlean < n && saving >= (double)kSplitRows;
     const int parts = split ? 2 : 1;
@@ -1956,7 +1977,7 @@ dpf_status launch_fused_batch(dpf_ctx ctx, int32_t n, const dpf_plan* plans, con
     for (int part = 0; part < parts; ++part) {
         int k = 0;
         for (int i = 0; i < n; ++i)
-            if (!split || (plans[i]->hq.lean.ok != 0) == (part == 0)) idx[k++] = i;
+            if (!split || use_lean(plans[i], o) == (part == 0)) idx[k++] = i;
         const dpf_status st = prepare_fused(ctx, k, idx, plans, o, ws, L[part]);
         if (st != DPF_OK) return st;
     }

@@ -333,3 +333,28 @@ def test_widest_values(ctx, col, rows):
         spec = _spec(f, ["k6"], aggs)
         G.say("widest values", col, rows, f)
         G.assert_same(G.run_gpu(db, spec), oracle.run(spec, {"t": t}), f"{col} {rows} {f}")
+
+
+# items that the caller wants small: the 32-bit kernel takes them from 2,048
+# rows on (two launches), and at any size where every row is kept
+@pytest.mark.parametrize("filt, plans, rows_per_item, launches", [
+    ([_lt(125)], 20, 1792, 1), ([_lt(125)], 20, 2048, 2), ([], 5, 256, 2)])
+def test_small_items(ctx, filt, plans, rows_per_item, launches):
+    import torch
+    from paper_2605_10511_amd import dpf
+    t = _table(1 << 20, 11)
+    tables = {"t": t, "d": {"k": np.arange(0, 9000, 2, dtype=np.int32)}}
+    semi = {**_spec([_lt(500)], ["k6"], [{"op": "COUNT"}]),
+            "probes": [{"fk": "k9k", "dim": "d", "key": "k", "filters": [], "payloads": []}]}
+    specs = [_spec(filt, ["k6"], [{"op": "COUNT"}, {"op": "SUM", "terms": [_s("b")]}]), semi]
+    want = [oracle.run(s, tables) for s in specs]
+    db = G.make_db(ctx, tables, {"t": ENC})
+    batch = [db.plan(specs[0]) for _ in range(plans)] + [db.plan(semi)]
+    G.say("small items", rows_per_item)
+    before = ctx.info().launches
+    res = dpf.execute(ctx, batch, rows_per_item=rows_per_item)
+    assert ctx.info().launches == before + launches
+    torch.cuda.synchronize()
+    for i in range(len(batch)):
+        G.assert_same(res.get(i), want[i == plans], f"plan {i}")
+    res.release()
