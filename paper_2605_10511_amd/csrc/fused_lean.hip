@@ -868,7 +868,7 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(4, 8
     uint32_t drained = 0;
     unsigned long long sink = 0;
     int cur = -1;
-    bool ok_hdr = true, values = true;  // values: set at a plan's start
+    bool ok_hdr = true, values = true;
     const bool guided = a.guided_mb != 0;
     for (bool first = true;; first = false) {
         int item = 0, mb0 = 0, mb1 = 0;
@@ -889,7 +889,7 @@ __global__ __launch_bounds__(16 * kWave) __attribute__((amdgpu_waves_per_eu(4, 8
         CQ& Q = *ro(a.q[qi]);
         if (qi != cur) {
             W.lr = (uint32_t)min(Q.lean.log2r, a.lean_log2r);
-            values = Q.lean.stage_first != 0;
+            if (!Q.lean.stage_first) values = false;
             cptr<uint4> src = (cptr<uint4>)&Q.lean.ents[0];
             uint4* dst = reinterpret_cast<uint4*>(shared_area + a.lds_shared);
             for (uint32_t e = threadIdx.x; e < (uint32_t)Q.lean.nents * sizeof(LeanEnt) / 16; e += blockDim.x)
