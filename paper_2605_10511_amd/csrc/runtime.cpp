@@ -944,12 +944,14 @@ constexpr int kLeanWavesPerCU = 16;         // lean kernel: 4 waves per SIMD (it
 // counted in scanned rows, 1 us a million, with kSplitKept more for a row that
 // the atoms keep (estimated from the columns' ranges) and kSplitRun where the
 // rows are in order of a group key in device memory (the general kernel adds
-// such rows one by one at one address).  One launch and two, us, beside a join
+// such rows one by one at one address), and kSplitPlan for a plan.  One launch and two, us, beside a join
 // over 250,000 rows: 2.2M rows, one in eight kept, 69 and 77; 8M 82 and 91; 32M
 // 166 and 146; 64M 290 and 215; 2M rows without atoms 77 and 82; 4.4M 105 and
-// 92; 2.2M by sorted day 733 and 104.
-constexpr int64_t kSplitRows = 40 << 20;
-constexpr double kSplitKept = 8, kSplitRun = 64;
+// 92; 2.2M by sorted day 733 and 104.  Filters and joins in turn over tables of
+// four sizes: 64 queries, 0.1 to 0.4M rows 341 and 376; 32, 0.1 to 1.6M 270 and
+// 286; 24, 0.15 to 4.8M 334 and 303; 48, 0.1 to 3.2M 489 and 430.
+constexpr int64_t kSplitRows = 34 << 20;
+constexpr double kSplitKept = 8, kSplitRun = 64, kSplitPlan = 3 << 18;
 
 // Places the plan's dimension tables and group table in the workgroup's LDS
 // shared area within budget; fills lds offsets and lds_shared.
@@ -1215,7 +1217,7 @@ double lean_saving(const dpf_plan_desc* desc, const DevQuery& q) {
     const double kept = kept_share(desc, q) * (double)q.nrows;
     const bool run = lean_runs(q);
     const double scanned = q.prune_mb ? (double)q.nlive * q.prune_mb * kMB : (double)q.nrows;
-    return scanned + (run ? kSplitRun : kSplitKept) * std::min(kept, scanned);
+    return kSplitPlan + scanned + (run ? kSplitRun : kSplitKept) * std::min(kept, scanned);
 }
 }  // namespace
 

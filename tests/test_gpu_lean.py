@@ -250,13 +250,13 @@ def test_refused_split_batch_leaves_no_trace(ctx):
         res.release()
 
 
-# scans beside a join plan: the batch is split once they save enough, 20 of
-# them that keep one row in eight, 5 that keep all, one in order of a key whose
+# scans beside a join plan: the batch is split once they save enough, 13 of
+# them that keep one row in eight, 4 that keep all, one in order of a key whose
 # table is in device memory; never for a sum of 64-bit values
 @pytest.mark.parametrize("filt, group, col, plans, split", [
-    ([_lt(125)], "k6", "b", 20, True), ([_lt(125)], "k6", "b", 19, False), ([], "k6", "b", 5, True),
-    ([], "k6", "b", 4, False), ([], "day", "b", 1, True), ([_lt(125)], "k6", "wide", 20, False),
-    ([_lt(125), {"col": "dkey", "op": "IN", "values": [11, 12, 400, 90000]}], "dkey", "dic", 20, True)])
+    ([_lt(125)], "k6", "b", 13, True), ([_lt(125)], "k6", "b", 12, False), ([], "k6", "b", 4, True),
+    ([], "k6", "b", 3, False), ([], "day", "b", 1, True), ([_lt(125)], "k6", "wide", 20, False),
+    ([_lt(125), {"col": "dkey", "op": "IN", "values": [11, 12, 400, 90000]}], "dkey", "dic", 13, True)])
 def test_split_launches(ctx, filt, group, col, plans, split):
     import torch
     from paper_2605_10511_amd import dpf
