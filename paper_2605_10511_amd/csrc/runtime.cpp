@@ -1064,7 +1064,11 @@ double kept_share(const dpf_plan_desc* desc, const DevQuery& q) {
 // modulo 2^64 once widened); no column with mini blocks wider than 32 bits, each
 // of which would be decoded by the general kernel's code between the lean steps
 // (full-width 64-bit columns, one row in eight kept: 98 us, in the general kernel
-// 89); no slot twice as a key.
+// 89); no slot twice as a key; no sums of a DELTA column wider than a bit over the
+// few rows of a selective scan: each such row is a walk of up to 255 differences,
+// which the lean kernel starts more often (2M rows, LDS group table, one in 250
+// kept 71 us in the general kernel and 107 here, one in 50 72 and 117; 8M rows, one
+// in 250 92 and 119, one in 50 97 and 127, one in 8 292 and 200).
 void fill_lean(const dpf_plan_desc* desc, DevQuery& q, const std::vector<int64_t>& lo, const std::vector<int64_t>& hi) {
     LeanPlan& L = q.lean;
     L.ok = 0;
@@ -1075,8 +1079,11 @@ void fill_lean(const dpf_plan_desc* desc, DevQuery& q, const std::vector<int64_t
     auto wide = [&](int col) { return desc->cols[col]->host.max_width > kLeanWidth; };
     for (int p = 0; p < q.npreds; ++p)
         if (wide(q.preds[p].col)) return;
-    for (int l = 0; l < q.nloads; ++l)
-        if (wide(q.loads[l].col)) return;
+    const bool few = kept_share(desc, q) < 0.05 && !q.agg_hash && q.ngroups * q.nacc * 8 <= kAggLdsMax;
+    for (int l = 0; l < q.nloads; ++l) {
+        const HostColumn& c = desc->cols[q.loads[l].col]->host;
+        if (wide(q.loads[l].col) || (few && c.enc == DPF_ENC_DELTA && c.max_width > 1)) return;
+    }
     auto view = [&](int col, int64_t ref) {
         const DevCol& c = q.cols[col];
         LeanMore e{};

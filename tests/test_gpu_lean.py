@@ -256,6 +256,7 @@ def test_refused_split_batch_leaves_no_trace(ctx):
 @pytest.mark.parametrize("filt, group, col, plans, split", [
     ([_lt(125)], "k6", "b", 13, True), ([_lt(125)], "k6", "b", 12, False), ([], "k6", "b", 4, True),
     ([], "k6", "b", 3, False), ([], "day", "b", 1, True), ([_lt(125)], "k6", "wide", 20, False),
+    ([_lt(50)], "k6", "ramp", 20, True), ([_lt(49)], "k6", "ramp", 20, False), ([_lt(49)], "day", "ramp", 20, True),
     ([_lt(125), {"col": "dkey", "op": "IN", "values": [11, 12, 400, 90000]}], "dkey", "dic", 13, True)])
 def test_split_launches(ctx, filt, group, col, plans, split):
     import torch
