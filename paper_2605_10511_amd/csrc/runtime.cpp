@@ -778,9 +778,15 @@ extern "C" dpf_status dpf_hash_build(dpf_ctx ctx, const dpf_hash_desc* desc, dpf
     uint8_t* scratch = (uint8_t*)ctx->alloc_mem(scratch_bytes, DPF_MEM_HBM);
     if (!scratch) return fail(DPF_ERR_OOM, "hash scratch");
     Guard guard{ctx, scratch, DPF_MEM_HBM};
+    // (a context whose allocator has no pinned memory left builds from pageable)
     uint8_t* stage = (uint8_t*)ctx->alloc_mem(scratch_bytes, DPF_MEM_HOST_MAPPED);
-    if (!stage) return fail(DPF_ERR_OOM, "hash staging");
     Guard stage_guard{ctx, stage, DPF_MEM_HOST_MAPPED};
+    std::unique_ptr<uint8_t[]> pageable;
+    if (!stage) {
+        pageable.reset(new (std::nothrow) uint8_t[scratch_bytes]);
+        stage = pageable.get();
+        if (!stage) return fail(DPF_ERR_OOM, "hash staging");
+    }
     A.count = (unsigned long long*)(scratch + cnt_off);
     A.mm = (long long*)(scratch + mm_off);
     A.status = (uint32_t*)(scratch + st_off);

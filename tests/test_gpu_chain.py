@@ -80,3 +80,27 @@ def test_chain_in_a_batch(ctx, chain):
         p.release()
         for h in p.hashes:
             h.release()
+
+
+def test_build_without_pinned_memory(monkeypatch):
+    """An allocator that hands out device memory only: columns in device memory
+    and hash builds over them need no more."""
+    from paper_2605_10511_amd import dpf
+
+    class DeviceOnly(dpf.TorchAllocator):
+        def _alloc(self, user, nbytes, kind):
+            return super()._alloc(user, nbytes, kind) if kind == dpf.DPF_MEM_HBM else None
+
+    monkeypatch.setattr(dpf, "TorchAllocator", DeviceOnly)
+    own = dpf.Context(0)
+    k = np.arange(5000, dtype=np.int32)
+    G.say("hash build, device memory only")
+    cols = {"k": dpf.Column(own, k), "p": dpf.Column(own, (k % 7).astype(np.int32))}
+    h = dpf.Hash(own, cols, "k", [{"col": "p", "op": "LT", "value": 3}], ["p"])
+    s = h.info()
+    assert s.entries == int((k % 7 < 3).sum())
+    assert (s.key_min, s.key_max, s.payload_min[0], s.payload_max[0]) == (0, int(k[k % 7 < 3].max()), 0, 2)
+    h.release()
+    for c in cols.values():
+        c.release()
+    own.close()
