@@ -356,8 +356,10 @@ typedef struct {
     int32_t mode;
     int32_t wg_per_cu;       /* FUSED: workgroups per compute unit (0 = auto)          */
     int32_t rows_per_item;   /* FUSED: rows per work item, multiple of 256 (0 = auto:   */
-                             /* at most 32768, one to three items per workgroup; in    */
-                             /* batches even slices of a pruned plan's blocks)          */
+                             /* one to three items per workgroup, in batches even       */
+                             /* slices of a pruned plan's blocks; at most 32768 rows,   */
+                             /* with string atoms and in batches 16384; for scans       */
+                             /* without probes and string atoms 4096 rows a wave)       */
     int32_t lds_hash_bytes;  /* FUSED: LDS budget for dimension tables (-1 = auto:     */
                              /* 72 KB, none for batches of more than 8 plans)          */
     int32_t waves_per_wg;    /* FUSED: 4, 8 or 16 waves per workgroup (0 = auto)       */
@@ -369,13 +371,14 @@ typedef struct {
 /* Enqueues n >= 1 plans on stream.  FUSED runs them all in ONE launch of the
  * persistent kernel, which claims (plan, row range) work items from a device
  * queue (two launches where some plans have probes or string atoms and the
- * others take tens of millions of rows; a plan whose group table is hashed or exceeds
- * 8,192 accumulators has its records written by a small launch more);
+ * others take tens of millions of rows; a plan whose group table is hashed or
+ * exceeds 8,192 accumulators has its records written by a small launch more);
  * FRAGMENTED runs each plan as a sequence of separate kernels with materialised
  * intermediates (it allocates on first use and is not meant for graph capture).
- * FUSED with n <= 64 allocates no device memory and is graph-capturable.  Outside stream capture the call records a completion
- * event on the stream for dpf_result_release.  A plan must not be in two
- * executions at once.  *out receives a result handle that is readable after
+ * FUSED with n <= 64 allocates no device memory and is graph-capturable; a
+ * batch that is refused has launched nothing.  Outside stream capture the call
+ * records a completion event on the stream for dpf_result_release.  A plan must
+ * not be in two executions at once.  *out receives a result handle that is readable after
  * the stream has synchronised. */
 dpf_status dpf_execute(dpf_ctx ctx, int32_t n, const dpf_plan* plans, const dpf_exec_opts* opts,
                        dpf_stream stream, dpf_result* out);

@@ -178,12 +178,10 @@ static_assert(sizeof(LeanEnt) == 80, "copied to LDS in 16-byte units");
 struct LeanMore {           // what only the rarer paths need of an entry
     const uint32_t* words;
     const uint32_t* woff;
-    const int64_t* base;
     const int64_t* dmin;
     int64_t ref;
     const int64_t* dict;    // value slot of a DICT column's values: u = dict[code] - dref
     int64_t dref;
-    uint32_t nwords;
     int32_t enc;
     int32_t ndict;
     int32_t col;            // index into DevQuery::cols

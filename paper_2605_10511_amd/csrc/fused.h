@@ -394,11 +394,11 @@ __device__ __forceinline__ uint32_t* ctr(const BatchArgs& a, int i) { return a.c
 // place in its range x, -1 when all are taken.  A workgroup's first item is its
 // place among those homed on its XCD; those after the last workgroup's are
 // claimed.  (Claims on one head are served one at a time, about 0.1 us each: 5M
-// comments, an item a workgroup, took 93 us with first items claimed too, 87
+// comments, an item a workgroup, took 99 us with first items claimed too, 93
 // without.)  Then the other ranges.  A lone plan with a few items a workgroup
 // reads the heads of all that are left together: one after the other they kept
 // every workgroup for seven waits at the launch's end (40,000 rows: 40.3 us,
-// now 37.3).  With many items (a.walk) ranges end at different times, and a
+// now 38.0).  With many items (a.walk) ranges end at different times, and a
 // workgroup looks for the next one often: there one head a look, or the reads
 // hold up the claims (two scans of 2.2M rows and four joins over 1M in one
 // batch: 113 us together, 99 so).

@@ -1,11 +1,13 @@
 // fused_lean.hip -- the fused kernel for batches whose plans carry every
-// value in 32 bits (LeanPlan: no probes, integer atoms only, each group key, measure and
-// payload an offset of less than 2^32 from its column's minimum, which holds
-// for all but plans over truly 64-bit columns).  fused.h has the general
-// kernel; both share the work queue, the group tables and the emission.
+// value in 32 bits (LeanPlan: no probes, integer atoms only, each group key and
+// measure an offset of less than 2^32 from its column's minimum, packed in 32
+// bits or fewer).  fused.h has the general kernel; both share the work queue, the
+// group tables and the emission.
 //
 // What bounds it: latency and instruction issue, not bandwidth (60M-row filter
-// 1.4 TB/s, 24M-row summary 0.7 TB/s of the 5.7 a plain read reaches).  The
+// 1.4 TB/s, 24M-row summary 0.8 TB/s of the 5.7 a plain read reaches; counters: a
+// mini block of the filter takes 263 vector and 266 scalar instructions, its
+// waves wait half of their cycles).  The
 // general kernel decodes to 64 bits, reads its descriptors with chains of
 // scalar loads for every mini block and again for every 64 surviving rows, and
 // adds each row to a group table that all lanes of a workgroup share, or to
@@ -25,8 +27,8 @@
 //    address;
 //  * rows of a wave that all fall in one group of a table in device memory
 //    (a sorted group key) are summed across the wave before one lane adds.
-// Before and after, kernel time: 60M-row filter 476 -> 209 us, 24M-row summary
-// 718 -> 168 us, revenue per day over 10M sorted rows 3,390 -> 105 us.
+// Before and after, kernel time: 60M-row filter 472 -> 208 us, 24M-row summary
+// 730 -> 157 us, revenue per day over 10M sorted rows 3,400 -> 91 us.
 #include "fused.h"
 
 namespace dpf {

@@ -1095,10 +1095,8 @@ void fill_lean(const dpf_plan_desc* desc, DevQuery& q, const std::vector<int64_t
         LeanMore e{};
         e.words = c.words;
         e.woff = c.woff;
-        e.base = c.base;
         e.dmin = c.dmin;
         e.ref = ref;
-        e.nwords = c.nwords;
         e.enc = c.enc;
         e.col = col;
         return e;
@@ -1147,12 +1145,13 @@ void fill_lean(const dpf_plan_desc* desc, DevQuery& q, const std::vector<int64_t
         L.stage_bytes += (int32_t)E.stage_sz + 16;
     }
     for (int e = 0; e < n; ++e) {
-        L.ents[e].words = L.more[e].words;
-        L.ents[e].woff = L.more[e].woff;
-        L.ents[e].base = L.more[e].base;
-        L.ents[e].dmin = L.more[e].dmin;
-        L.ents[e].nwords = L.more[e].nwords;
-        L.ents[e].enc = L.more[e].enc;
+        const DevCol& c = q.cols[L.more[e].col];
+        L.ents[e].words = c.words;
+        L.ents[e].woff = c.woff;
+        L.ents[e].base = c.base;
+        L.ents[e].dmin = c.dmin;
+        L.ents[e].nwords = c.nwords;
+        L.ents[e].enc = c.enc;
     }
     // (the same slot twice as a key: the general kernel)
     for (int k = 0; k < q.nkeys; ++k) {
@@ -1843,7 +1842,7 @@ dpf_status prepare_fused(dpf_ctx ctx, int32_t n, const int32_t* idx, const dpf_p
         if (best) {
             set_lean(best_group, best_log2r);
             waves = best_w;
-        } else {  // its LDS does not fit beside the dimension tables
+        } else {  // its LDS does not fit (waves_per_wg asked for)
             lean = false;
             a.lds_shared = general_shared;
         }
